@@ -380,8 +380,9 @@ int mnb_timer_end(int64_t* launches, double* ms, double* flops, double* bytes);
  *                            of forward cones
  *   MNB_VAR_NO_FIRST_CONV    first-layer convolutions (stride 1, at most 4 input
  *                            channels) through the general kernels
- *   MNB_VAR_NO_WIN_CONV      forward convolutions through the gather GEMM instead of
- *                            the input-window kernel
+ *   MNB_VAR_NO_WIN_CONV      convolutions through the FP32 kernels (row-resident or
+ *                            gather GEMM) instead of the input-window kernel on split
+ *                            operands
  * The initial mask comes from the environment variables MNB_BOTTOM_VALU,
  * MNB_NO_TAP_CONVT, MNB_NO_PAIR_CONV, MNB_NO_ROW_CONV, MNB_NO_WIN_BOTTOM,
  * MNB_NO_FUSED_BOTTOM, MNB_NO_PATCH, MNB_NO_CONE, MNB_NO_FIRST_CONV and

@@ -235,19 +235,6 @@ static void fill_conv_geom(mnb_net* net, ConvGeom& g, int Ci, int Hi, int Wi, in
                             wf[(size_t)co * g.Ci * k * k + (size_t)t * g.Ci + cg * 16 + c];
         g.Wg = upload(wg.data(), wg.size(), &net->owned);
     }
-    g.Wt = nullptr;
-    if (g.Ci % 8 == 0) {
-        // the input-window kernel stages 8 input channels at a time: per group, per tap, per
-        // channel a row of Co filter weights
-        std::vector<float> wt(wf.size());
-        for (int cg = 0; cg < g.Ci / 8; ++cg)
-            for (int t = 0; t < k * k; ++t)
-                for (int c = 0; c < 8; ++c)
-                    for (int co = 0; co < g.Co; ++co)
-                        wt[(((size_t)cg * k * k + t) * 8 + c) * g.Co + co] =
-                            Wh[((size_t)co * g.Ci + cg * 8 + c) * k * k + t];
-        g.Wt = upload(wt.data(), wt.size(), &net->owned);
-    }
     // stride phases of the transposed convolution
     MNB_CHECK(s * s <= 16, MNB_EINVAL, "conv stride above 4 is not supported");
     g.n_phase = 0;
@@ -291,49 +278,16 @@ static void fill_conv_geom(mnb_net* net, ConvGeom& g, int Ci, int Hi, int Wi, in
                                         wp[((size_t)tt * g.Co + cg * 16 + c) * g.Ci + ci];
                     ph.Wpg = upload(wg.data(), wg.size(), &net->owned);
                 }
-                ph.Wt = nullptr;
-                if (g.Co % 8 == 0) {
-                    // the phase as a stride-1 correlation for the input-window kernel: tap
-                    // (Ty-1-ty, Tx-1-tx) reads coefficient (q0y + i - ty, q0x + j - tx)
-                    std::vector<float> wt(wp.size());
-                    for (int cg = 0; cg < g.Co / 8; ++cg)
-                        for (int ty = 0; ty < ph.Ty; ++ty)
-                            for (int tx = 0; tx < ph.Tx; ++tx)
-                                for (int c = 0; c < 8; ++c)
-                                    for (int ci = 0; ci < g.Ci; ++ci) {
-                                        const int t = (ph.Ty - 1 - ty) * ph.Tx + (ph.Tx - 1 - tx);
-                                        wt[(((size_t)cg * T + t) * 8 + c) * g.Ci + ci] =
-                                            wp[((size_t)(ty * ph.Tx + tx) * g.Co + cg * 8 + c) * g.Ci + ci];
-                                    }
-                    ph.Wt = upload(wt.data(), wt.size(), &net->owned);
-                }
             }
             g.ph[g.n_phase++] = ph;
         }
-    g.Wt4 = nullptr;
-    bool same = s == 2 && g.n_phase == 4 && g.Co % 8 == 0;
-    for (int f = 0; same && f < 4; ++f)
-        same = g.ph[f].Wt && g.ph[f].Ty > 0 && g.ph[f].Ty == g.ph[f].Tx && g.ph[f].Ty == g.ph[0].Ty &&
-               g.ph[f].nY == g.ph[0].nY && g.ph[f].nX == g.ph[0].nX && g.ph[f].nY > 0 && g.ph[f].nX > 0;
-    if (same) {
-        // phase f's block of each 8-channel group follows phase f - 1's (the host copy of ph[f].Wt is
-        // rebuilt here from the same weights)
-        const int T = g.ph[0].Ty * g.ph[0].Tx;
-        std::vector<float> w4((size_t)g.Co * 4 * T * g.Ci);
-        for (int f = 0; f < 4; ++f) {
-            const ConvPhase& ph = g.ph[f];
-            for (int cg = 0; cg < g.Co / 8; ++cg)
-                for (int ty = 0; ty < ph.Ty; ++ty)
-                    for (int tx = 0; tx < ph.Tx; ++tx)
-                        for (int c = 0; c < 8; ++c)
-                            for (int ci = 0; ci < g.Ci; ++ci) {
-                                const int t = (ph.Ty - 1 - ty) * ph.Tx + (ph.Tx - 1 - tx);
-                                const int co = cg * 8 + c;
-                                w4[((((size_t)cg * 4 + f) * T + t) * 8 + c) * g.Ci + ci] =
-                                    Wh[(((size_t)co * g.Ci + ci) * k + (ph.rho_y + s * ty)) * k + (ph.rho_x + s * tx)];
-                            }
-        }
-        g.Wt4 = upload(w4.data(), w4.size(), &net->owned);
+    // filter streams of the split-operand kernel
+    for (bool back : {false, true}) {
+        const size_t bytes = split_stream_bytes(g, back);
+        if (bytes == 0) continue;
+        void* w = dalloc(bytes);
+        net->owned.push_back(w);
+        launch_split_stream(g, back, w, stream());
     }
 }
 

@@ -458,6 +458,7 @@ static bool launch_convT_small(const ConvGeom& g, const float* A, float* C, int 
 void launch_conv_backsub(const ConvGeom& g, const float* A, float* C, int M, bool accumulate,
                          hipStream_t st) {
     if (M <= 0) return;
+    if (launch_conv_backsub_split(g, A, C, M, accumulate, st)) return;
     if (launch_conv_backsub_rows(g, A, C, M, accumulate, st)) return;
     if (launch_convT_first(g, A, C, M, accumulate, st)) return;
     if (launch_convT_small(g, A, C, M, accumulate, st)) return;
@@ -468,7 +469,6 @@ void launch_conv_backsub(const ConvGeom& g, const float* A, float* C, int M, boo
         MNB_HIP(hipGetLastError());
         return;
     }
-    if (launch_conv_backsub_win(g, A, C, M, accumulate, st)) return;
     for (int f = 0; f < g.n_phase; ++f) {
         const ConvPhase& ph = g.ph[f];
         if (ph.nY <= 0 || ph.nX <= 0) continue;
@@ -489,10 +489,10 @@ void launch_conv_backsub(const ConvGeom& g, const float* A, float* C, int M, boo
 void launch_conv_forward(const ConvGeom& g, const float* G, float* C, int M, bool accumulate,
                          hipStream_t st, const ConeClip* clip) {
     if (M <= 0) return;
+    if (launch_conv_forward_split(g, G, C, M, accumulate, st, clip)) return;
     // the row-resident kernels write no clip
     if (!clip && launch_conv_forward_rows(g, G, C, M, accumulate, st)) return;
     if (launch_conv_first(g, G, C, M, accumulate, st, clip)) return;
-    if (launch_conv_forward_win(g, G, C, M, accumulate, st, clip)) return;
     ConvFwd p;
     p.clip = clip ? *clip : ConeClip{};
     p.A = G; p.C = C; p.bias = g.b; p.ktab = g.fwd_ktab;

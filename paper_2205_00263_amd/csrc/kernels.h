@@ -15,7 +15,14 @@ struct ConvPhase {
     const float* Wp;    // [Ty][Tx][Co][Ci] weights of the phase
     const float* Wpg;   // the same with K ordered (co / 16, ty, tx, co % 16) (Co % 16 == 0)
     const int2* ktab;   // [Ty*Tx*Co] {co*Ho*Wo - ty*Wo - tx, (ty<<16)|tx}
-    const float* Wt;    // [Co/8][Ty*Tx][8][Ci] flipped taps for the input-window kernel (Co % 8 == 0)
+};
+
+// One direction of a convolution on the split-operand kernel (conv_split.hip): its access pattern,
+// the padding of window row and column 0, the 8-channel groups per LDS stage (0: not covered), the
+// reduction steps per stage and the filters cut into bf16 parts in the order the kernel reads them.
+struct SplitConv {
+    int pat, pad, cgs, nstep;
+    const unsigned char* w;
 };
 
 struct ConvGeom {
@@ -25,12 +32,9 @@ struct ConvGeom {
     const int2* fwd_ktab;  // [k*k*Ci] {ci*Hi*Wi + ky*Wi + kx, (ky<<16)|kx}, K ordered (ky, kx, ci)
     const float* Wf;       // [Co][k*k*Ci] weights in that K order
     const float* Wg;       // [Co][k*k*Ci] weights with K ordered (ci / 16, ky, kx, ci % 16) (Ci % 16 == 0)
-    const float* Wt;       // [Ci/8][k*k][8][Co] weights of the input-window kernel (Ci % 8 == 0)
-    // stride 2 with four phases of equal grid and square taps T x T: their flipped taps side by
-    // side, [Co/8][4][T*T][8][Ci] (Co % 8 == 0), for the transposed window kernel; else null
-    const float* Wt4;
     int n_phase;
     ConvPhase ph[16];   // stride <= 4
+    SplitConv sf, sb;   // forward and transposed
 };
 
 // Rows held on forward cones (receptive-field rows): a forward convolution given a clip writes 0
@@ -67,14 +71,15 @@ bool launch_conv_forward_rows(const ConvGeom& g, const float* G, float* C, int M
 bool launch_convT_first(const ConvGeom& g, const float* A, float* C, int M, bool accumulate, hipStream_t st);
 bool launch_conv_first(const ConvGeom& g, const float* G, float* C, int M, bool accumulate, hipStream_t st,
                        const ConeClip* clip = nullptr);
-// Forward convolution from input windows staged in LDS (8 input channels at a time, Co % 32 == 0,
-// 3x3 / 1, 3x3 / 2 or 4x4 / 2 filters); false (nothing launched) for other shapes.
-bool launch_conv_forward_win(const ConvGeom& g, const float* G, float* C, int M, bool accumulate, hipStream_t st,
-                             const ConeClip* clip = nullptr);
-// Transposed convolution by the same kernel, one stride phase at a time (each phase is a stride-1
-// correlation of the coefficient grid with the phase's flipped taps; square phases of 2x2 or 3x3
-// taps, Co % 8 == 0, Ci % 32 == 0); false (nothing launched) for other shapes.
-bool launch_conv_backsub_win(const ConvGeom& g, const float* A, float* C, int M, bool accumulate, hipStream_t st);
+// Convolutions on the bf16 matrix instructions with exactly split FP32 operands, from input windows
+// staged in LDS (input channels a multiple of 8, output channels of 16; 3x3 / 1, 2x2 / 1, 3x3 / 2,
+// 4x4 / 2 and 1x1 / 2 filters); false (nothing launched) for other shapes.  split_stream_bytes plans a direction and gives the size of its filter stream (0: not
+// covered), launch_split_stream fills it.
+size_t split_stream_bytes(ConvGeom& g, bool back);
+void launch_split_stream(ConvGeom& g, bool back, void* out, hipStream_t st);
+bool launch_conv_forward_split(const ConvGeom& g, const float* G, float* C, int M, bool accumulate, hipStream_t st,
+                               const ConeClip* clip = nullptr);
+bool launch_conv_backsub_split(const ConvGeom& g, const float* A, float* C, int M, bool accumulate, hipStream_t st);
 
 // ---- forward products (adjoint and upper-bound evaluation) ----
 // C[M, dout] = G[M, din] * W^T + b  (accumulate: C += ..., bias added either way)
