@@ -572,15 +572,17 @@ int row_grid(long M) {
 
 }  // namespace
 
-// Tap-GEMM form of the transposed convolution for small input grids; false when the shape
-// does not fit it.
-static bool launch_convT_tap(const ConvGeom& g, const float* A, float* C, int M, bool accumulate, hipStream_t st) {
+bool launch_convT_tap(const ConvGeom& g, const float* A, float* C, int M, bool accumulate, hipStream_t st) {
     const bool off = (kernel_variants() & (MNB_VAR_NO_TAP_CONVT | MNB_VAR_NO_ROW_CONV)) != 0;
     const int HoWo = g.Ho * g.Wo, HiWi = g.Hi * g.Wi;
     if (off || g.s != 2 || g.k > 4 || g.Co != 32 || HoWo > 32 || HiWi > 192 || g.Ci < 2) return false;
     ConvTTapArgs a{};
     a.A = A; a.C = C; a.W = g.W; a.M = M; a.acc = accumulate;
     a.Ci = g.Ci; a.Hi = g.Hi; a.Wi = g.Wi; a.Co = g.Co; a.Ho = g.Ho; a.Wo = g.Wo; a.k = g.k; a.s = g.s; a.p = g.p;
+    // grids of at most 16 positions, and more input channels than 16, gain from the split-operand kernel's
+    // shared windows where it covers the shape (8192 rows of 32x2x2 -> 32x6x6: 26 us against 69; 48000 of
+    // 32x5x5 -> 16x13x13: 368 against 290)
+    if ((HoWo <= 16 || g.Ci > 16) && g.sb.w && !(kernel_variants() & MNB_VAR_NO_WIN_CONV)) return false;
     const int mt = (HoWo + 15) / 16, nq = (HiWi + 63) / 64;
     const size_t lds = ((size_t)g.Ci * g.Co * 16 + (size_t)(TT / 64) * 2 * (16 * mt + 1) * TLD) * sizeof(float);
     if (lds > ROW_LDS_MAX) return false;
@@ -600,7 +602,6 @@ static bool launch_convT_tap(const ConvGeom& g, const float* A, float* C, int M,
 
 bool launch_conv_backsub_rows(const ConvGeom& g, const float* A, float* C, int M, bool accumulate,
                               hipStream_t st) {
-    if (launch_convT_tap(g, A, C, M, accumulate, st)) return true;
     const bool off = (kernel_variants() & MNB_VAR_NO_ROW_CONV) != 0;
     if (off || g.Ci % 16 != 0 || (g.Co != 16 && g.Co != 32 && g.Co != 64) || g.n_phase > 4) return false;
     const int rowA = g.Co * g.Ho * g.Wo;

@@ -871,6 +871,11 @@ struct PassChunk {
     int* win_ptr_d = nullptr;
     WinEnt* win_ent_d = nullptr;
     int M = 0;                  // rows
+    int max_rows() const {      // of an instance
+        int n = 0;
+        for (const InstDesc& i : inst) n = std::max(n, i.r1 - i.r0);
+        return n;
+    }
     const RowDesc* rows = nullptr;   // device, chunk-relative row order
     std::vector<InstDesc> inst;      // host, rows relative to the chunk
     InstDesc* inst_d = nullptr;
@@ -944,6 +949,7 @@ struct PassCtx {
     // rows +-e_j on a fully connected layer's output not materialised: the first fold of the
     // pass reads sign W[j] (fold_W, fold_b: weights and objective bias; consumed by that fold)
     const float* fold_W = nullptr;
+    const ConvGeom* fold_conv = nullptr;   // the layer is this convolution
     const float* fold_b = nullptr;
     const RowDesc* fold_rows = nullptr;
     // receptive-field rows: a' deviation windows per relu node [M, window]; the shared rows'
@@ -1044,6 +1050,7 @@ static void walk_backsub(PassCtx& cx, const PassChunk& ch, BufPool& pool, std::m
                 fa.inst = ch.inst_d; fa.n_inst = (int)ch.inst.size();
                 fa.slots = cx.slots_d;
                 fa.M = M; fa.d = nd.size;
+                fa.max_rows = ch.max_rows();
                 fa.l = pb->l + net->relu_off[m]; fa.u = pb->u + net->relu_off[m];
                 fa.S = pb->S_ + net->relu_off[m]; fa.ld_state = pb->ld_state;
                 fa.alpha = pb->alpha + net->relu_off[m]; fa.beta = pb->beta + net->relu_off[m];
@@ -1056,7 +1063,13 @@ static void walk_backsub(PassCtx& cx, const PassChunk& ch, BufPool& pool, std::m
                     fa.rows = cx.fold_rows;
                     fa.c = cx.c;
                     fa.bias_obj = cx.fold_b;
+                    if (cx.fold_conv) {
+                        const ConvGeom& g = *cx.fold_conv;
+                        fa.ck = g.k; fa.cs = g.s; fa.cp = g.p;
+                        fa.cHo = g.Ho; fa.cWo = g.Wo; fa.cHi = g.Hi; fa.cWi = g.Wi; fa.cCi = g.Ci;
+                    }
                     cx.fold_W = nullptr;
+                    cx.fold_conv = nullptr;
                 }
                 {
                     TimerScope ts(MNB_T_FOLD, n, 0.0, (double)M * node_width(net, ch, n) * (store_ap ? 12 : 8));
@@ -1133,20 +1146,31 @@ static float* run_backsub(PassCtx& cx, const PassChunk& ch, BufPool& pool, bool 
             MNB_CHECK(!coef.count(a.src), MNB_EINVAL, "objective operands share a producer");
             coef[a.src] = A;
         };
-        if (o.kind == MNB_ADD) {
-            init_aff(o.src, true);
-            init_aff(o.src2, false);
-        } else if (o.kind == MNB_FC && net->nodes[o.src].kind == MNB_RELU && cx.ckpt_stride <= 1) {
-            // the rows are sign W[j] on the FC input: the ReLU fold that comes first reads them
-            // from W (no checkpoint copies this coefficient before that fold)
-            coef[o.src] = pool.acquire();
-            cx.fold_W = o.Wd;
+        // An affine node whose input is the first ReLU of the pass: its rows are sign W[j] (windows of the
+        // filter for a convolution) on that ReLU's output, and the fold that comes first reads them from
+        // the weights (no checkpoint copies this coefficient before that fold).
+        top = pass_top(net, ch.obj_layer);
+        auto direct = [&](int n) {
+            const NetNode& a = net->nodes[n];
+            // (indices of a convolution's rows go through FP32: exact below 2^21)
+            if (a.src != top || top <= stop || net->nodes[top].kind != MNB_RELU || cx.ckpt_stride > 1 || a.size >= 1 << 21)
+                return false;
+            coef[a.src] = pool.acquire();
+            cx.fold_W = a.Wd;
+            cx.fold_conv = a.kind == MNB_CONV ? &a.geom : nullptr;
             cx.fold_b = be;
             cx.fold_rows = ch.rows;
-        } else {
+            return true;
+        };
+        if (o.kind == MNB_ADD) {
+            // (init_aff refuses operands that share a producer before either is used)
+            MNB_CHECK(net->nodes[o.src].src != net->nodes[o.src2].src, MNB_EINVAL, "objective operands share a producer");
+            const bool d1 = direct(o.src), d2 = !d1 && direct(o.src2);
+            if (!d1) init_aff(o.src, !d2);
+            if (!d2) init_aff(o.src2, false);
+        } else if (!direct(on)) {
             init_aff(on, true);
         }
-        top = pass_top(net, ch.obj_layer);
     }
     int col = 0;
     walk_backsub(cx, ch, pool, coef, top, stop, store_ap, col, true);
@@ -1249,6 +1273,9 @@ static void run_adjoint(PassCtx& cx, const PassChunk& ch, BufPool& pool, float* 
                 const bool mnc = pb->has_mnc;
                 ra.gsum_hat = mnc ? gs_hat : nullptr;
                 ra.gsum_out = mnc ? gs_out : nullptr;
+                ra.n_slices = relax_slices(nd.size, n_inst, ch.max_rows());
+                if (ra.n_slices > 1)
+                    ra.part = cx.ws->get<float>("relax_part", (size_t)ra.n_slices * n_inst * 3 * nd.size);
                 {
                     TimerScope ts(MNB_T_RELAX, n, 0.0, 12.0 * M * nd.size);
                     launch_relu_relax(ra, st);

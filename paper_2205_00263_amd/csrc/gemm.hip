@@ -458,6 +458,7 @@ static bool launch_convT_small(const ConvGeom& g, const float* A, float* C, int 
 void launch_conv_backsub(const ConvGeom& g, const float* A, float* C, int M, bool accumulate,
                          hipStream_t st) {
     if (M <= 0) return;
+    if (launch_convT_tap(g, A, C, M, accumulate, st)) return;
     if (launch_conv_backsub_split(g, A, C, M, accumulate, st)) return;
     if (launch_conv_backsub_rows(g, A, C, M, accumulate, st)) return;
     if (launch_convT_first(g, A, C, M, accumulate, st)) return;

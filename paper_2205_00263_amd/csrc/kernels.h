@@ -60,6 +60,9 @@ void launch_fc_backsub(const float* A, const float* W, float* C, int M, int dout
 // C[M, Ci*Hi*Wi] (+)= conv-transpose of A[M, Co*Ho*Wo]
 void launch_conv_backsub(const ConvGeom& g, const float* A, float* C, int M, bool accumulate,
                          hipStream_t st);
+// Tap-GEMM form of the transposed convolution for small input grids; false (nothing launched) when
+// the shape does not fit it or another kernel serves it better.
+bool launch_convT_tap(const ConvGeom& g, const float* A, float* C, int M, bool accumulate, hipStream_t st);
 // Row-resident MFMA forms of the two convolution products, used by launch_conv_backsub /
 // launch_conv_forward when a row fits in LDS; false (nothing launched) otherwise.
 bool launch_conv_backsub_rows(const ConvGeom& g, const float* A, float* C, int M, bool accumulate,
@@ -146,11 +149,16 @@ struct FoldArgs {
     // a = sign W[j] is read from Wsrc instead of A, and c[r] = sign bias_obj[j] is written
     // (nullable: a is read from A)
     const float* Wsrc; const RowDesc* rows; float* c; const float* bias_obj;
+    // the same for rows +-e_j on the output of a convolution (Wsrc its filters [Co][d's channels][k][k];
+    // ck = 0: fully connected): a = sign W[co][ci][ky][kx] where the neuron lies in j's window, else 0
+    int ck, cs, cp, cHo, cWo, cHi, cWi, cCi;
     // receptive-field rows: per instance and neuron {D(a' >= 0), D(a' < 0), b-underline, a'} of the
     // instance's shared row [n_inst, d] (A holds windows of the deviation from it); rt_out
     // (nullable) receives that table from a fold of the shared rows (one row per instance)
     const float4* rt_in;
     float4* rt_out;
+    int max_rows;         // most rows of an instance
+    int slice_rows;       // set by the launch
 };
 void launch_relu_fold(const FoldArgs& a, hipStream_t st);
 
@@ -169,10 +177,13 @@ struct RelaxArgs {
     // an instance's rows are spread over many wavefronts): slice z of instance i writes partial sums
     // at slot zoff[i] + z of part [zoff[n_inst]][3][d], which launch_relax_sum adds in slice order,
     // so every sum has an order fixed by the instance alone; n_slices: most slices of an instance
+    // (zoff null: n_slices slots for every instance; n_slices <= 1 in a whole-row relaxation: no slices)
     const int* zoff; int n_slices; float* part;
 };
 constexpr int kRowSlice = 64;
 void launch_relu_relax(const RelaxArgs& a, hipStream_t st);
+// row slices of a whole-row relaxation (1: none); a.part then holds n_slices x n_inst x 3 x d floats
+int relax_slices(int d, int n_inst, int max_rows);
 // d_alpha, d_beta and the gamma sums from the slices' partial sums in a.part
 void launch_relax_sum(const RelaxArgs& a, hipStream_t st);
 void launch_relu_fold(const FoldArgs& a, hipStream_t st, const float* gp);

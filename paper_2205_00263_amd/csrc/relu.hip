@@ -34,15 +34,29 @@ __global__ __launch_bounds__(256) void k_relu_fold(FoldArgs a, const float* gp) 
     // empty asm keeps their loads above the wait.
     asm volatile("" ::: "memory");
     vmem_drain();
+    // rows of a convolution's output: this neuron's channel and padded position
+    int cch = 0, cY = 0, cX = 0;
+    float rHW = 0.f, rW = 0.f;
+    if (a.ck) {
+        cch = jj / (a.cHi * a.cWi);
+        const int q = jj - cch * a.cHi * a.cWi;
+        cY = q / a.cWi;
+        cX = q - cY * a.cWi + a.cp;
+        cY += a.cp;
+        rHW = 1.f / (float)(a.cHo * a.cWo);
+        rW = 1.f / (float)a.cWo;
+    }
     // rows in groups of FR with all of a group's loads in flight together
     constexpr int FR = 8;
-    for (int r0 = in.r0; r0 < in.r1; r0 += FR) {
+    // this slice of the instance's rows (rows are independent of each other here)
+    const int first = in.r0 + (int)blockIdx.z * a.slice_rows, r1 = min(first + a.slice_rows, in.r1);
+    for (int r0 = first; r0 < r1; r0 += FR) {
         float av[FR];
         if (a.Wsrc) {
             // the group's row descriptors {b, inst, j, sign} as 16-byte loads, all in flight together
             int4 rdv[FR];
 #pragma unroll
-            for (int u = 0; u < FR; ++u) rdv[u] = reinterpret_cast<const int4*>(a.rows)[min(r0 + u, in.r1 - 1)];
+            for (int u = 0; u < FR; ++u) rdv[u] = reinterpret_cast<const int4*>(a.rows)[min(r0 + u, r1 - 1)];
             float sg[FR];
             int jr[FR];
 #pragma unroll
@@ -51,19 +65,30 @@ __global__ __launch_bounds__(256) void k_relu_fold(FoldArgs a, const float* gp) 
                 jr[u] = rdv[u].z;
             }
             // every lane loads (rows past the instance read its last row's filter, lanes past d
-            // column 0), so that the loads are in flight together; the value is then selected
+            // column 0, neurons outside a row's window the filter's first weight), so that the loads are
+            // in flight together; the value is then selected
 #pragma unroll
             for (int u = 0; u < FR; ++u) {
-                const float w = a.Wsrc[(long)jr[u] * a.d + jj];
-                av[u] = (ok && r0 + u < in.r1) ? sg[u] * w : 0.f;
+                long at = (long)jr[u] * a.d + jj;
+                if (a.ck) {
+                    const int j_ = __builtin_amdgcn_readfirstlane(jr[u]);
+                    const int co = (int)(((float)j_ + 0.5f) * rHW), q = j_ - co * a.cHo * a.cWo;
+                    const int yo = (int)(((float)q + 0.5f) * rW), xo = q - yo * a.cWo;
+                    const int ky = cY - a.cs * yo, kx = cX - a.cs * xo;
+                    const bool in_win = ky >= 0 && ky < a.ck && kx >= 0 && kx < a.ck;
+                    at = ((long)co * a.cCi + cch) * a.ck * a.ck + (in_win ? ky * a.ck + kx : 0);
+                    if (!in_win) sg[u] = 0.f;
+                }
+                const float w = a.Wsrc[at];
+                av[u] = (ok && r0 + u < r1) ? sg[u] * w : 0.f;
             }
-            if (blockIdx.x == 0 && threadIdx.x < FR && r0 + (int)threadIdx.x < in.r1) {
-                const int u = threadIdx.x;
-                a.c[r0 + u] = sg[u] * a.bias_obj[jr[u]];
+            if (blockIdx.x == 0 && threadIdx.x < FR && r0 + (int)threadIdx.x < r1) {
+                const RowDesc rd = a.rows[r0 + threadIdx.x];
+                a.c[r0 + threadIdx.x] = (float)rd.sign * a.bias_obj[rd.j];
             }
         } else {
 #pragma unroll
-            for (int u = 0; u < FR; ++u) av[u] = (ok && r0 + u < in.r1) ? a.A[(long)(r0 + u) * a.d + j] : 0.f;
+            for (int u = 0; u < FR; ++u) av[u] = (ok && r0 + u < r1) ? a.A[(long)(r0 + u) * a.d + j] : 0.f;
         }
         // the group's values complete before its first store: no later wait (which would also
         // wait for the stores before it) is left pending inside the row steps
@@ -71,7 +96,7 @@ __global__ __launch_bounds__(256) void k_relu_fold(FoldArgs a, const float* gp) 
 #pragma unroll
         for (int u = 0; u < FR; ++u) {
             const int r = r0 + u;
-            if (r >= in.r1) break;
+            if (r >= r1) break;
             float contrib = 0.f;
             if (ok) {
                 const long e = (long)r * a.d + j;
@@ -93,8 +118,17 @@ __global__ __launch_bounds__(256) void k_relu_fold(FoldArgs a, const float* gp) 
 
 void launch_relu_fold(const FoldArgs& a, hipStream_t st, const float* gp) {
     if (a.n_inst <= 0) return;
-    dim3 grid(cdiv(a.d, 256), a.n_inst);
-    hipLaunchKernelGGL(k_relu_fold, grid, dim3(256), 0, st, a, gp);
+    // a thread walks its instance's rows, so a few instances of many rows (a root's layer, octahedral
+    // rows) would leave the chip idle: their rows are cut into slices of at least 32 until there are
+    // about 4096 workgroups, twice what the chip holds at a time.  2496 rows of 8192 neurons of one
+    // instance: 155 us in one piece
+    const long blocks = (long)cdiv(a.d, 256) * a.n_inst;
+    const int most = std::max(a.max_rows, 1);
+    const int nz = std::min({cdiv(most, 32), cdiv(4096, blocks), kMaxGridY});
+    FoldArgs f = a;
+    f.slice_rows = cdiv(most, nz);
+    dim3 grid(cdiv(a.d, 256), a.n_inst, cdiv(most, f.slice_rows));
+    hipLaunchKernelGGL(k_relu_fold, grid, dim3(256), 0, st, f, gp);
     MNB_HIP(hipGetLastError());
 }
 void launch_relu_fold(const FoldArgs& a, hipStream_t st) { launch_relu_fold(a, st, nullptr); }
@@ -103,6 +137,10 @@ void launch_relu_fold(const FoldArgs& a, hipStream_t st) { launch_relu_fold(a, s
 // Forward image of the concretisation minimiser through a row's relaxation:
 // g = D ghat + b-underline, with the parameter gradients of the row's set
 //   d alpha_j = sum_r [unstable, a'_rj >= 0] a'_rj ghat_rj,  d beta_j = S_j sum_r ghat_rj.
+// The sums run over slices of kRowSlice rows, each in row order, the slices' totals then added in
+// order: the same value whether one workgroup walks all slices of an instance or each slice has its
+// own (SLICED: the totals go to a.part, which launch_relax_sum adds).
+template <bool SLICED>
 __global__ __launch_bounds__(256) void k_relu_relax(RelaxArgs a) {
     const InstDesc in = a.inst[blockIdx.y];
     const int j = blockIdx.x * 256 + threadIdx.x;
@@ -112,27 +150,44 @@ __global__ __launch_bounds__(256) void k_relu_relax(RelaxArgs a) {
     const int s = (int)a.S[so];
     NeuronRelax nr = neuron_relax(a.l[so], a.u[so], s, a.alpha[po]);
     float da = 0.f, sh = 0.f, sg = 0.f;
-    // rows in groups of RR with all of a group's loads in flight together; sums in row order
-    constexpr int RR = 16;
-    for (int r0 = in.r0; r0 < in.r1; r0 += RR) {
-        float ghv[RR], apv[RR];
+    const int first = SLICED ? in.r0 + (int)blockIdx.z * kRowSlice : in.r0;
+    const int last = SLICED ? min(first + kRowSlice, in.r1) : in.r1;
+    for (int z0 = first; z0 < last; z0 += kRowSlice) {
+        const int z1 = min(z0 + kRowSlice, last);
+        float zda = 0.f, zsh = 0.f, zsg = 0.f;
+        // rows in groups of RR with all of a group's loads in flight together
+        constexpr int RR = 16;
+        for (int r0 = z0; r0 < z1; r0 += RR) {
+            float ghv[RR], apv[RR];
 #pragma unroll
-        for (int u = 0; u < RR; ++u) {
-            const long e = (long)min(r0 + u, in.r1 - 1) * a.d + j;
-            ghv[u] = a.G[e];
-            apv[u] = a.Ap[e];
-        }
+            for (int u = 0; u < RR; ++u) {
+                const long e = (long)min(r0 + u, z1 - 1) * a.d + j;
+                ghv[u] = a.G[e];
+                apv[u] = a.Ap[e];
+            }
 #pragma unroll
-        for (int u = 0; u < RR; ++u) {
-            if (r0 + u >= in.r1) break;
-            const float gh = ghv[u], ap = apv[u];
-            const bool neg = ap < 0.f;
-            const float g = (neg ? nr.dneg : nr.dpos) * gh + (neg ? nr.bneg : 0.f);
-            a.G[(long)(r0 + u) * a.d + j] = g;
-            if (nr.unstable && !neg) da += ap * gh;
-            sh += gh;
-            sg += g;
+            for (int u = 0; u < RR; ++u) {
+                if (r0 + u >= z1) break;
+                const float gh = ghv[u], ap = apv[u];
+                const bool neg = ap < 0.f;
+                const float g = (neg ? nr.dneg : nr.dpos) * gh + (neg ? nr.bneg : 0.f);
+                a.G[(long)(r0 + u) * a.d + j] = g;
+                if (nr.unstable && !neg) zda += ap * gh;
+                zsh += gh;
+                zsg += g;
+            }
         }
+        da += zda;
+        sh += zsh;
+        sg += zsg;
+    }
+    if (SLICED) {
+        if (first >= last) return;
+        float* pz = a.part + ((long)blockIdx.y * a.n_slices + blockIdx.z) * 3 * a.d;
+        pz[j] = da;
+        pz[a.d + j] = sh;
+        pz[2 * a.d + j] = sg;
+        return;
     }
     const long go = (long)blockIdx.y * a.ldg + a.goff + j;
     a.d_alpha[go] = da;
@@ -149,7 +204,10 @@ __global__ __launch_bounds__(256) void k_relax_sum(RelaxArgs a) {
     if (n >= a.d) return;
     const InstDesc in = a.inst[li];
     float da = 0.f, sh = 0.f, sg = 0.f;
-    for (int z = a.zoff[li]; z < a.zoff[li + 1]; ++z) {
+    // without slot offsets every instance has n_slices slots
+    const int z0 = a.zoff ? a.zoff[li] : li * a.n_slices;
+    const int z1 = a.zoff ? a.zoff[li + 1] : z0 + (in.r1 - in.r0 + kRowSlice - 1) / kRowSlice;
+    for (int z = z0; z < z1; ++z) {
         const float* pz = a.part + (long)z * 3 * a.d;
         da += pz[n];
         sh += pz[a.d + n];
@@ -167,10 +225,24 @@ void launch_relax_sum(const RelaxArgs& a, hipStream_t st) {
     MNB_HIP(hipGetLastError());
 }
 
+// A few instances of many rows get a workgroup per slice (502 rows of one instance on 32768 neurons
+// run in 128 workgroups otherwise), unless the slices' sums would take more than 64 MiB.
+int relax_slices(int d, int n_inst, int max_rows) {
+    const long nz = cdiv(max_rows, kRowSlice);
+    if (nz <= 1 || nz > kMaxGridY || (long)cdiv(d, 256) * n_inst >= 1024) return 1;
+    return nz * n_inst * 3 * d * 4 <= (64l << 20) ? (int)nz : 1;
+}
+
 void launch_relu_relax(const RelaxArgs& a, hipStream_t st) {
     if (a.n_inst <= 0) return;
-    dim3 grid(cdiv(a.d, 256), a.n_inst);
-    hipLaunchKernelGGL(k_relu_relax, grid, dim3(256), 0, st, a);
+    const dim3 grid(cdiv(a.d, 256), a.n_inst, std::max(a.n_slices, 1));
+    if (a.n_slices > 1) {
+        hipLaunchKernelGGL(k_relu_relax<true>, grid, dim3(256), 0, st, a);
+        MNB_HIP(hipGetLastError());
+        launch_relax_sum(a, st);
+        return;
+    }
+    hipLaunchKernelGGL(k_relu_relax<false>, grid, dim3(256), 0, st, a);
     MNB_HIP(hipGetLastError());
 }
 
@@ -403,54 +475,93 @@ void launch_init_oct(const int32_t* grp, int n_groups, int d, const float* bias,
 
 // ------------------------------------------------------------------ interval propagation
 // center/radius form of one affine node: c' = W c + b, r' = |W| r.
-__global__ void k_ibp_fc(const float* W, const float* b, const float* L, const float* U, float* Lo, float* Uo,
-                         int din, int dout) {
-    int n = blockIdx.x * blockDim.x + threadIdx.x;
+// One wavefront per output: a thread per output (the form before) walks din serially, which on the
+// few outputs of a layer leaves the chip idle (294 us for 4096 -> 512, 52 us for 784 -> 100).
+__device__ __forceinline__ double wave_sum_double(double v) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    return v;
+}
+__global__ __launch_bounds__(256) void k_ibp_fc(const float* W, const float* b, const float* L, const float* U, float* Lo,
+                                                float* Uo, int din, int dout) {
+    const int n = blockIdx.x * 4 + (threadIdx.x >> 6);
     if (n >= dout) return;
     double c = 0.0, rad = 0.0;
     const float* w = W + (long)n * din;
-    for (int k = 0; k < din; ++k) {
+    for (int k = threadIdx.x & 63; k < din; k += 64) {
         double m = 0.5 * ((double)L[k] + (double)U[k]);
         double h = 0.5 * ((double)U[k] - (double)L[k]);
         c += (double)w[k] * m;
         rad += fabs((double)w[k]) * h;
     }
+    c = wave_sum_double(c);
+    rad = wave_sum_double(rad);
+    if ((threadIdx.x & 63) != 0) return;
     c += b[n];
     Lo[n] = (float)(c - rad);
     Uo[n] = (float)(c + rad);
 }
-__global__ void k_ibp_conv(const float* W, const float* b, const float* L, const float* U, float* Lo,
-                           float* Uo, int Ci, int Hi, int Wi, int Co, int Ho, int Wo, int k, int s, int p) {
-    int n = blockIdx.x * blockDim.x + threadIdx.x;
-    if (n >= Co * Ho * Wo) return;
-    int co = n / (Ho * Wo), pos = n - co * Ho * Wo;
-    int y = pos / Wo, x = pos - y * Wo;
+// 16 outputs of one channel's plane per workgroup, the input channels dealt to NS threads each
+// (NS = 16, or 1 for the few channels of a first layer, 256 outputs per workgroup then); their sums are
+// added in order.  4096 outputs of 1024 terms: 155 us with a thread each.
+template <int NS>
+__global__ __launch_bounds__(256) void k_ibp_conv(const float* W, const float* b, const float* L, const float* U,
+                                                  float* Lo, float* Uo, int Ci, int Hi, int Wi, int Ho, int Wo, int k,
+                                                  int s, int p) {
+    constexpr int NO = 256 / NS;
+    __shared__ double sum[2][NS > 1 ? 256 : 1];
+    const int o = threadIdx.x % NO, sl = threadIdx.x / NO;
+    const int co = blockIdx.y, pos = blockIdx.x * NO + o;
+    const bool ok = pos < Ho * Wo;
+    const int y = pos / Wo, x = pos - y * Wo;
     double c = 0.0, rad = 0.0;
-    for (int ci = 0; ci < Ci; ++ci)
-        for (int ky = 0; ky < k; ++ky)
-            for (int kx = 0; kx < k; ++kx) {
-                int Y = s * y - p + ky, X = s * x - p + kx;
-                if (Y < 0 || Y >= Hi || X < 0 || X >= Wi) continue;
-                long e = ((long)ci * Hi + Y) * Wi + X;
-                double w = W[(((long)co * Ci + ci) * k + ky) * k + kx];
-                c += w * 0.5 * ((double)L[e] + (double)U[e]);
-                rad += fabs(w) * 0.5 * ((double)U[e] - (double)L[e]);
-            }
+    if (ok)
+        for (int ci = sl; ci < Ci; ci += NS)
+            for (int ky = 0; ky < k; ++ky)
+                for (int kx = 0; kx < k; ++kx) {
+                    int Y = s * y - p + ky, X = s * x - p + kx;
+                    if (Y < 0 || Y >= Hi || X < 0 || X >= Wi) continue;
+                    long e = ((long)ci * Hi + Y) * Wi + X;
+                    double w = W[(((long)co * Ci + ci) * k + ky) * k + kx];
+                    c += w * 0.5 * ((double)L[e] + (double)U[e]);
+                    rad += fabs(w) * 0.5 * ((double)U[e] - (double)L[e]);
+                }
+    if (NS > 1) {
+        sum[0][threadIdx.x] = c;
+        sum[1][threadIdx.x] = rad;
+        __syncthreads();
+        if (sl != 0) return;
+        for (int t = 1; t < NS; ++t) {
+            c += sum[0][t * NO + o];
+            rad += sum[1][t * NO + o];
+        }
+    }
+    if (!ok) return;
     c += b[co];
+    const long n = (long)co * Ho * Wo + pos;
     Lo[n] = (float)(c - rad);
     Uo[n] = (float)(c + rad);
 }
 void launch_ibp_fc(const float* W, const float* b, const float* L, const float* U, float* Lo, float* Uo,
                    int din, int dout, hipStream_t st) {
-    hipLaunchKernelGGL(k_ibp_fc, dim3(cdiv(dout, 128)), dim3(128), 0, st, W, b, L, U, Lo, Uo, din, dout);
+    hipLaunchKernelGGL(k_ibp_fc, dim3(cdiv(dout, 4)), dim3(256), 0, st, W, b, L, U, Lo, Uo, din, dout);
     MNB_HIP(hipGetLastError());
 }
 void launch_ibp_conv(const ConvGeom& g, const float* L, const float* U, float* Lo, float* Uo,
                      hipStream_t st) {
-    int n = g.Co * g.Ho * g.Wo;
-    hipLaunchKernelGGL(k_ibp_conv, dim3(cdiv(n, 128)), dim3(128), 0, st, g.W, g.b, L, U, Lo, Uo, g.Ci, g.Hi,
-                       g.Wi, g.Co, g.Ho, g.Wo, g.k, g.s, g.p);
-    MNB_HIP(hipGetLastError());
+    const int P = g.Ho * g.Wo;
+    for (int c0 = 0; c0 < g.Co; c0 += kMaxGridY) {
+        const int nc = std::min(g.Co - c0, kMaxGridY);
+        const float* w = g.W + (long)c0 * g.Ci * g.k * g.k;
+        const long o = (long)c0 * P;
+        if (g.Ci >= 8)
+            hipLaunchKernelGGL(k_ibp_conv<16>, dim3(cdiv(P, 16), nc), dim3(256), 0, st, w, g.b + c0, L, U, Lo + o, Uo + o,
+                               g.Ci, g.Hi, g.Wi, g.Ho, g.Wo, g.k, g.s, g.p);
+        else
+            hipLaunchKernelGGL(k_ibp_conv<1>, dim3(cdiv(P, 256), nc), dim3(256), 0, st, w, g.b + c0, L, U, Lo + o, Uo + o,
+                               g.Ci, g.Hi, g.Wi, g.Ho, g.Wo, g.k, g.s, g.p);
+        MNB_HIP(hipGetLastError());
+    }
 }
 // relu of an interval, intersected with known input bounds (lk/uk nullable)
 __global__ void k_ibp_relu(const float* L, const float* U, const float* lk, const float* uk, float* Lo,
