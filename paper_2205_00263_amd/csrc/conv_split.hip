@@ -11,13 +11,14 @@
 // are staged, the filters once, when the net is created.
 //
 // Rounding.  The instruction adds groups of eight products with the lower bits of the smaller ones cut
-// off downwards: every sum comes out a little low (1e-8 of its terms), the same way for every output,
-// and over the inputs of a network that adds up (the bounds of ConvBig's fourth layer moved by 1.5e-6,
-// seven times their FP32 error).  So the accumulators change sign half way through each stage and the
-// filters of the second half enter negated: the two halves' errors cancel (bounds within 3.2e-7 of the
-// FP64 ones, 2.3e-7 by FP32 instructions, and both means below 3e-8), for one negation per accumulator
-// and stage.  Error of one layer against FP64 (random operands): 2.4e-7 where FP32 instructions give
-// 3.0e-7 (32x16x16 -> 64, 3x3).
+// off downwards: every sum of the leading products comes out a little low (1e-8 of its terms), the same
+// way for every output, and over the inputs of a network that adds up (the bounds of ConvBig's fourth
+// layer moved by 1.5e-6, seven times their FP32 error).  So the accumulators change sign half way
+// through each stage and the filters of the second half enter negated: the two halves' errors cancel.
+// The five small part products have accumulators of their own, added at the end, so that they do not
+// round the large sum once more each.  Error of a layer against FP64: 7.6e-8, 1.1e-7 and 5.6e-8 back
+// through ConvBig's three layers, where the FP32 instructions give 2.1e-7, 3.2e-7 and 1.4e-7 (mean of the
+// errors 1e-10 of the values in both); of the fourth layer's bounds 2.0e-7 against 2.3e-7.
 //
 // Work split.  One workgroup owns BM output positions (part of a row's grid, or the whole grids of R
 // rows) and BN filters.  Per stage of CGS 8-channel groups it writes the input window those positions
@@ -32,9 +33,9 @@
 // An output sums its stages, window offsets and part products in an order fixed by the layer, whatever
 // the batch and tile: a row's result does not depend on the rows around it.
 //
-// What bounds it: 2048 rows of 32x16x16 -> 64 (3x3) take 95 us (203 TFLOP/s; 207 us on the FP32
-// instructions); without its global loads and stores the kernel takes 75 us, with them alone 40.
-// 32x32x32 -> 32x16x16 (4x4 / 2): 121 us against 203, at 2.8 TB/s.
+// What bounds it: 2048 rows of 32x16x16 -> 64 (3x3) take 98 us (198 TFLOP/s; 207 us on the FP32
+// instructions before); without its global loads and stores the kernel takes 75 us, with them alone 40.
+// 32x32x32 -> 32x16x16 (4x4 / 2): 134 us against 203 at 2.5 TB/s, back 142 us against 225.
 #include "kernels.h"
 #include "../../include/mnbab.h"
 
@@ -164,11 +165,13 @@ __device__ __forceinline__ void split8(const float* x, uintx4& h, uintx4& m, uin
 template <class PT, int NP, int S, int CGS, int FN, int FM, int WN, int WM>
 __global__ __launch_bounds__(64 * WN * WM, (FN * FM * NP >= 8 ? 2 : 3)) void k_conv_split(SplitArgs a) {
     constexpr int NT = 64 * WN * WM, UT = 4 / CGS, BM = 16 * FM * WM;
-    // 4x4 / 2 filters into 32 channels: keep the next step's reads ahead of this step's matrix
-    // instructions (the small stages leave few wavefronts to hide them: 140 against 126 TFLOP/s at
-    // 32x32x32 -> 16x16x32); elsewhere the compiler's own order needs fewer registers and is faster
-    // (32x16x16 -> 64 3x3: 211 against 191)
-    constexpr bool AHEAD = S == 2 && PT::cnt(0) == 4 && FN * WN < 4;
+    // Whether the next step's reads are held ahead of this step's matrix instructions (left to itself the
+    // compiler moves them down to their use, which needs fewer registers).  Ahead against not, TFLOP/s:
+    // 3x3 / 1 with two position fragments a wavefront 173 / 157 (16x16 -> 32), 170 / 163 (8x8), with four
+    // 186 / 193; 4x4 / 2 into 64 channels 187 / 177, into 32 127 / 127; 3x3 / 2 114 / 108 and 89 / 91;
+    // transposed 4x4 / 2 115 / 120, 121 / 95, 156 / 133, transposed 3x3 / 2 91 / 98
+    constexpr bool AHEAD = NP == 2 ? PT::cnt(0) == 2 && PT::cnt(1) == 2
+                           : S == 1 ? FM <= 2 : PT::cnt(0) > 1 && FN * WN >= 4;
     extern __shared__ unsigned char sm[];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave % WM, wn = wave / WM;
@@ -178,7 +181,7 @@ __global__ __launch_bounds__(64 * WN * WM, (FN * FM * NP >= 8 ? 2 : 3)) void k_c
         rows = min(a.R, a.M - r0);
     } else {
         r0 = blockIdx.x / a.mtiles; m0 = (blockIdx.x - r0 * a.mtiles) * BM;
-        y_first = qdiv(m0, a.rWo);
+        y_first = __builtin_amdgcn_readfirstlane(qdiv(m0, a.rWo));
         rows = 1;
     }
     const int n0 = blockIdx.y * (16 * FN * WN);
@@ -210,13 +213,13 @@ __global__ __launch_bounds__(64 * WN * WM, (FN * FM * NP >= 8 ? 2 : 3)) void k_c
     }
     const int zero_at = CGS * a.plane * POSB;
 
-    floatx4 acc[NP * NP][FN][FM];
+    floatx4 acc[NP * NP][FN][FM], low[NP * NP][FN][FM];
 #pragma unroll
     for (int f = 0; f < NP * NP; ++f)
 #pragma unroll
         for (int j = 0; j < FN; ++j)
 #pragma unroll
-            for (int i = 0; i < FM; ++i) acc[f][j][i] = floatx4{0.f, 0.f, 0.f, 0.f};
+            for (int i = 0; i < FM; ++i) acc[f][j][i] = low[f][j][i] = floatx4{0.f, 0.f, 0.f, 0.f};
 
     // reduction steps of a stage
     constexpr int NSTEP = StepTable<PT, NP, UT>{}.n;
@@ -234,7 +237,9 @@ __global__ __launch_bounds__(64 * WN * WM, (FN * FM * NP >= 8 ? 2 : 3)) void k_c
 
     for (int g = 0; g < a.ng; ++g) {
         __syncthreads();   // previous stage consumed (or the zero fill done)
-        const float* src = a.G + (long)r0 * a.ldG + (long)g * (CGS * 8) * HiWi + (long)(iy0 + wy_lo) * a.Wi;
+        // one base address per channel of a group and a 32-bit offset per thread, shared by the eight loads
+        const char* src = reinterpret_cast<const char*>(a.G + (long)r0 * a.ldG + (long)g * (CGS * 8) * HiWi +
+                                                        (long)(iy0 + wy_lo) * a.Wi);
         for (int e0 = tid; e0 < total; e0 += 2 * NT) {
             float x[2][8];
             int dst[2];
@@ -246,9 +251,10 @@ __global__ __launch_bounds__(64 * WN * WM, (FN * FM * NP >= 8 ? 2 : 3)) void k_c
                 const int c = CGS > 1 ? qdiv(er, rpc) : 0;
                 const int rem = er - c * per_c;
                 const int row = qdiv(rem, a.rWi), col = rem - row * a.Wi;
-                const float* s = src + (long)rl * a.ldG + (long)c * 8 * HiWi + rem;
+                const unsigned at = (unsigned)(rl * (int)a.ldG + c * 8 * HiWi + rem) * 4u;
 #pragma unroll
-                for (int k = 0; k < 8; ++k) x[h][k] = s[(long)k * HiWi];
+                for (int k = 0; k < 8; ++k)
+                    x[h][k] = *reinterpret_cast<const float*>(src + (long)k * HiWi * 4 + at);
                 dst[h] = (c * a.plane + (rl * a.WH + wy_lo + row) * a.RS + a.p + col) * POSB;
             }
 #pragma unroll
@@ -280,16 +286,19 @@ __global__ __launch_bounds__(64 * WN * WM, (FN * FM * NP >= 8 ? 2 : 3)) void k_c
             const int cb = T.set[t] & 1, cu = t & 1, f = T.ph[t];
             if (t + 1 < NSTEP && T.set[t + 1] != T.set[t]) { MNB_LOADB(T.set[t + 1] & 1, t + 1) }
             if constexpr (AHEAD) __builtin_amdgcn_sched_barrier(0);
-#define MNB_MM(sa, sb)                                                                               \
+#define MNB_MM(to, sa, sb)                                                                           \
     _Pragma("unroll") for (int j = 0; j < FN; ++j) _Pragma("unroll") for (int i = 0; i < FM; ++i)     \
-        acc[f][j][i] = NP == 1 ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(bf[cb][i][sb], ab[cu][j][sa], acc[f][j][i], 0, 0, 0) \
-                                   : __builtin_amdgcn_mfma_f32_16x16x32_bf16(ab[cu][j][sa], bf[cb][i][sb], acc[f][j][i], 0, 0, 0);
-            MNB_MM(2, 0) MNB_MM(1, 1) MNB_MM(0, 2) MNB_MM(1, 0) MNB_MM(0, 1) MNB_MM(0, 0)
+        to[f][j][i] = NP == 1 ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(bf[cb][i][sb], ab[cu][j][sa], to[f][j][i], 0, 0, 0) \
+                                   : __builtin_amdgcn_mfma_f32_16x16x32_bf16(ab[cu][j][sa], bf[cb][i][sb], to[f][j][i], 0, 0, 0);
+            MNB_MM(low, 2, 0) MNB_MM(acc, 0, 0) MNB_MM(low, 1, 1) MNB_MM(low, 0, 2) MNB_MM(low, 1, 0) MNB_MM(low, 0, 1)
             if (T.flip[t]) {
 #pragma unroll
                 for (int j = 0; j < FN; ++j)
 #pragma unroll
-                    for (int i = 0; i < FM; ++i) acc[f][j][i] = -acc[f][j][i];
+                    for (int i = 0; i < FM; ++i) {
+                        acc[f][j][i] = -acc[f][j][i];
+                        low[f][j][i] = -low[f][j][i];
+                    }
             }
             if constexpr (AHEAD) __builtin_amdgcn_sched_barrier(0);
         }
@@ -305,6 +314,12 @@ __global__ __launch_bounds__(64 * WN * WM, (FN * FM * NP >= 8 ? 2 : 3)) void k_c
 #undef MNB_MM
 
     const int oHW = a.oH * a.oW;
+#pragma unroll
+    for (int f = 0; f < NP * NP; ++f)
+#pragma unroll
+        for (int j = 0; j < FN; ++j)
+#pragma unroll
+            for (int i = 0; i < FM; ++i) acc[f][j][i] += low[f][j][i];
     const float sgn = a.ng & 1 ? -1.f : 1.f;   // the accumulators change sign once a stage
     if constexpr (NP == 1) {
         // result lanes: filter 16 j + lane % 16, positions 4 (lane / 16) + v of fragment i, which go
@@ -542,9 +557,8 @@ int tiles_for(int pat, int Cout, Tile* t) {
         else if (Cout % 32 == 0) { t[n++] = Tile{2, 2, 1, 4}; t[n++] = Tile{2, 4, 1, 4}; t[n++] = Tile{2, 1, 1, 4}; }
         else { t[n++] = Tile{1, 2, 1, 4}; t[n++] = Tile{1, 4, 1, 4}; }
     } else {
-        if (Cout % 64 == 0) { t[n++] = Tile{1, 4, 4, 1}; t[n++] = Tile{1, 2, 4, 1}; }
-        else if (Cout % 32 == 0) { t[n++] = Tile{1, 4, 2, 2}; t[n++] = Tile{1, 2, 2, 2}; }
-        else { t[n++] = Tile{1, 2, 1, 4}; t[n++] = Tile{1, 4, 1, 4}; }
+        // (two position fragments a wavefront: with four, the four phases' accumulators leave no registers)
+        t[n++] = Cout % 64 == 0 ? Tile{1, 2, 4, 1} : Cout % 32 == 0 ? Tile{1, 2, 2, 2} : Tile{1, 2, 1, 4};
     }
     return n;
 }
@@ -565,9 +579,7 @@ void launch_pat(const Tile& t, int cgs, dim3 grid, size_t lds, const SplitArgs& 
         MNB_SPC(2, 2, 1, 4) MNB_SPC(2, 4, 1, 4) MNB_SPC(2, 1, 1, 4)
         MNB_SPC(1, 2, 1, 4) MNB_SPC(1, 4, 1, 4)
     } else {
-        MNB_SPC(1, 4, 4, 1) MNB_SPC(1, 2, 4, 1)
-        MNB_SPC(1, 4, 2, 2) MNB_SPC(1, 2, 2, 2)
-        MNB_SPC(1, 2, 1, 4) MNB_SPC(1, 4, 1, 4)
+        MNB_SPC(1, 2, 4, 1) MNB_SPC(1, 2, 2, 2) MNB_SPC(1, 2, 1, 4)
     }
 #undef MNB_SPC
 #undef MNB_SP
