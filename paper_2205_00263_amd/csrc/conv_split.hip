@@ -37,19 +37,12 @@
 // instructions before); without its global loads and stores the kernel takes 75 us, with them alone 40.
 // 32x32x32 -> 32x16x16 (4x4 / 2): 134 us against 203 at 2.5 TB/s, back 142 us against 225.
 #include "kernels.h"
+#include "split.h"
 #include "../../include/mnbab.h"
 
 namespace mnb {
 namespace {
 
-typedef float floatx4 __attribute__((ext_vector_type(4)));
-typedef float floatx2 __attribute__((ext_vector_type(2)));
-typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-
-constexpr int POSB = 48;              // LDS bytes of one window position: 3 parts x 8 channels x 2
-constexpr int STEPB = 3 * 64 * 16;    // bytes of one reduction step of a 16-filter fragment
 constexpr size_t SPLIT_LDS_MAX = 80 * 1024;
 
 struct SplitArgs {
@@ -131,36 +124,6 @@ struct StepTable {
         }
     }
 };
-
-// Eight floats into three bf16 octets, each part the nearest to what the parts before it leave, so
-// that the products left out have no sign in common (cut off instead, they pull every sum towards
-// zero by 4e-8, which thousands of rows do not average out).  Values that would round up to an
-// infinity are cut off; infinities and NaN keep their value in the first part and zero (NaN) in the
-// others.
-__device__ __forceinline__ void split8(const float* x, uintx4& h, uintx4& m, uintx4& l) {
-    float big = 0.f;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) big = fmaxf(big, fabsf(x[i]));
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const floatx2 v = {x[2 * i], x[2 * i + 1]};
-        unsigned p = __builtin_bit_cast(unsigned, __builtin_convertvector(v, bf16x2));
-        if (big >= 3.3895e38f) {
-            if (fabsf(v[0]) >= 3.3895e38f) p = (p & 0xffff0000u) | __float_as_uint(v[0]) >> 16;
-            if (fabsf(v[1]) >= 3.3895e38f) p = (p & 0xffffu) | (__float_as_uint(v[1]) & 0xffff0000u);
-        }
-        floatx2 r = {v[0] - __uint_as_float(p << 16), v[1] - __uint_as_float(p & 0xffff0000u)};
-        if (big >= 3.3895e38f) {
-            if (fabsf(v[0]) == INFINITY) r[0] = 0.f;
-            if (fabsf(v[1]) == INFINITY) r[1] = 0.f;
-        }
-        const unsigned q = __builtin_bit_cast(unsigned, __builtin_convertvector(r, bf16x2));
-        const floatx2 t = {r[0] - __uint_as_float(q << 16), r[1] - __uint_as_float(q & 0xffff0000u)};
-        h[i] = p;
-        m[i] = q;
-        l[i] = __builtin_bit_cast(unsigned, __builtin_convertvector(t, bf16x2));
-    }
-}
 
 template <class PT, int NP, int S, int CGS, int FN, int FM, int WN, int WM>
 __global__ __launch_bounds__(64 * WN * WM, (FN * FM * NP >= 8 ? 2 : 3)) void k_conv_split(SplitArgs a) {
@@ -430,16 +393,7 @@ __global__ __launch_bounds__(256) void k_split_stream(StreamArgs a, long n) {
         if ((g & 1) != (int)(a.late >> t & 1)) w = -w;
     }
     unsigned short* dst = a.out + rest * (STEPB / 2) + lane * 8 + j;
-    float r = w;
-#pragma unroll
-    for (int s = 0; s < 3; ++s) {
-        unsigned h = __float_as_uint(r) >> 16;
-        r -= __uint_as_float(h << 16);
-        // a part of a nonzero weight is never zero (the smallest normal instead), so that an infinite
-        // operand gives the infinity an FP32 product gives and no 0 x inf
-        if (w != 0.f && (h & 0x7fff) == 0) h = (__float_as_uint(w) >> 16 & 0x8000) | 0x0080;
-        dst[s * 512] = (unsigned short)h;
-    }
+    split_weight(w, dst);
 }
 
 enum { PAT_F31, PAT_F21, PAT_F42, PAT_F32, PAT_F12, PAT_T42D, PAT_T42S, PAT_T32D, PAT_T32S, PAT_T12 };

@@ -65,6 +65,7 @@ struct NetNode {
     float* Wd = nullptr;
     float* bd = nullptr;
     ConvGeom geom{};
+    unsigned char *fc_back = nullptr, *fc_fwd = nullptr;   // filter streams of a fully connected node
     int relu_m = -1;
     double macs_per_row = 0;   // nonzero multiply-adds of the layer for one row
 };

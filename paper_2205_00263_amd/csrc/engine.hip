@@ -517,6 +517,13 @@ extern "C" int mnb_net_create(const mnb_layer* L_in, int n_in, mnb_net** out) {
                         nd.C = l.out_chw[0]; nd.H = 1; nd.W = 1;
                         const int din = in.C * in.H * in.W;
                         nd.Wd = upload(l.W, (size_t)nd.C * din, &net->owned);
+                        for (bool back : {false, true}) {
+                            const int N = back ? (int)din : nd.C, K = back ? nd.C : (int)din;
+                            unsigned char* w = (unsigned char*)dalloc(fc_stream_bytes(N, K));
+                            net->owned.push_back(w);
+                            launch_fc_stream(nd.Wd, N, K, back, w, stream());
+                            (back ? nd.fc_back : nd.fc_fwd) = w;
+                        }
                         nd.bd = upload(l.b, (size_t)nd.C, &net->owned);
                         nd.macs_per_row = (double)nd.C * din;
                         break;
@@ -1033,7 +1040,7 @@ static void walk_backsub(PassCtx& cx, const PassChunk& ch, BufPool& pool, std::m
                                   2.0 * M * (ch.pp ? ch.pp->macs[n] : nd.macs_per_row),
                                   4.0 * M * (node_width(net, ch, n) + node_width(net, ch, dst) * (acc ? 2 : 1)));
                     if (nd.kind == MNB_FC)
-                        launch_fc_backsub(a, nd.Wd, out, M, nd.size, net->nodes[dst].size, acc, st);
+                        launch_fc_backsub(nd.fc_back, a, out, M, nd.size, net->nodes[dst].size, acc, st);
                     else
                         launch_conv_backsub(ch.pp ? ch.pp->conv[n] : nd.geom, a, out, M, acc, st);
                 }
@@ -1238,7 +1245,7 @@ static void run_adjoint(PassCtx& cx, const PassChunk& ch, BufPool& pool, float* 
                     TimerScope ts(nd.kind == MNB_FC ? MNB_T_FC_FORWARD : MNB_T_CONV_FORWARD, n,
                                   2.0 * M * nd.macs_per_row, 4.0 * M * (nd.size + net->nodes[nd.src].size));
                     if (nd.kind == MNB_FC)
-                        launch_fc_forward(g[nd.src], nd.Wd, nd.bd, out, M, net->nodes[nd.src].size, nd.size, false,
+                        launch_fc_forward(nd.fc_fwd, g[nd.src], nd.bd, out, M, net->nodes[nd.src].size, nd.size, false,
                                           st);
                     else
                         launch_conv_forward(nd.geom, g[nd.src], out, M, false, st);

@@ -1,10 +1,9 @@
-// FP32 MFMA products of back-substitution (Eq. 2) and of its adjoint.
+// FP32 MFMA convolutions of back-substitution (Eq. 2) and of its adjoint, for the shapes the
+// split-operand kernel (conv_split.hip) does not take.
 //
 // One generic LDS-staged GEMM  C[m, n] = sum_k A(m, k) B(k, n)  on
 // v_mfma_f32_16x16x4_f32, 256 threads (4 wavefronts of 64), with the operand
 // element maps supplied by a small "problem" class:
-//   FcBack   A = coefficient rows [M, dout], B = W [dout, din]            (a W)
-//   FcFwd    A = forward rows [M, din],      B(k, n) = W[n, k]            (g W^T + b)
 //   ConvBack A(m, k) gathers the coefficient of the conv output that feeds
 //            input position m through tap k (one stride phase per launch:
 //            implicit-GEMM transposed convolution), B = phase weights
@@ -20,47 +19,6 @@ typedef float floatx4 __attribute__((ext_vector_type(4)));
 constexpr int BK = 16;
 
 // ------------------------------------------------------------------ problems
-struct FcBack {
-    static constexpr bool A_MFAST = false;   // A contiguous along k
-    static constexpr bool B_NFAST = true;    // B contiguous along n
-    const float* A; const float* W; float* C;
-    int M, N, K; int acc;
-    struct MCtx { long base, cbase; bool ok; };
-    __device__ MCtx mctx(int m) const { return {(long)m * K, (long)m * N, m < M}; }
-    __device__ float a(const MCtx& c, int k) const { return (c.ok && k < K) ? A[c.base + k] : 0.f; }
-    __device__ float b(int k, int n) const { return (k < K && n < N) ? W[(long)k * N + n] : 0.f; }
-    static constexpr int tile_ok = 0;
-    template <int NA>
-    __device__ void a_tile(const MCtx&, int, const int*, float*) const {}
-    __device__ void store_ctx(const MCtx& c, int n, float v) const {
-        if (c.ok && n < N) {
-            float* p = C + c.cbase + n;
-            *p = acc ? *p + v : v;
-        }
-    }
-};
-
-struct FcFwd {
-    static constexpr bool A_MFAST = false;
-    static constexpr bool B_NFAST = false;   // B(k, n) = W[n*K + k], contiguous along k
-    const float* A; const float* W; const float* bias; float* C;
-    int M, N, K; int acc;
-    struct MCtx { long base, cbase; bool ok; };
-    __device__ MCtx mctx(int m) const { return {(long)m * K, (long)m * N, m < M}; }
-    __device__ float a(const MCtx& c, int k) const { return (c.ok && k < K) ? A[c.base + k] : 0.f; }
-    __device__ float b(int k, int n) const { return (k < K && n < N) ? W[(long)n * K + k] : 0.f; }
-    static constexpr int tile_ok = 0;
-    template <int NA>
-    __device__ void a_tile(const MCtx&, int, const int*, float*) const {}
-    __device__ void store_ctx(const MCtx& c, int n, float v) const {
-        if (c.ok && n < N) {
-            float* p = C + c.cbase + n;
-            v += bias[n];
-            *p = acc ? *p + v : v;
-        }
-    }
-};
-
 struct ConvBack {
     static constexpr bool A_MFAST = true;
     static constexpr bool B_NFAST = true;
@@ -311,22 +269,6 @@ static void run_gemm(const P& p, hipStream_t st) {
         hipLaunchKernelGGL((k_gemm<128, 128, 2, P>), grid, blk, 0, st, p);
     }
     MNB_HIP(hipGetLastError());
-}
-
-void launch_fc_backsub(const float* A, const float* W, float* C, int M, int dout, int din,
-                       bool accumulate, hipStream_t st) {
-    if (M <= 0) return;
-    FcBack p;
-    p.A = A; p.W = W; p.C = C; p.M = M; p.N = din; p.K = dout; p.acc = accumulate;
-    run_gemm(p, st);
-}
-
-void launch_fc_forward(const float* G, const float* W, const float* b, float* C, int M, int din,
-                       int dout, bool accumulate, hipStream_t st) {
-    if (M <= 0) return;
-    FcFwd p;
-    p.A = G; p.W = W; p.bias = b; p.C = C; p.M = M; p.N = dout; p.K = din; p.acc = accumulate;
-    run_gemm(p, st);
 }
 
 // ------------------------------------------------------------------ small-Ci transposed conv (VALU)

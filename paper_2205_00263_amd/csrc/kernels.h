@@ -54,9 +54,13 @@ __device__ __forceinline__ void cone_origin(const ConeClip& k, long r, int& oy, 
 }
 
 // ---- back-substitution products (Eq. 2) ----
-// C[M, din] (+)= A[M, dout] * W[dout, din]
-void launch_fc_backsub(const float* A, const float* W, float* C, int M, int dout, int din,
-                       bool accumulate, hipStream_t st);
+// Filter stream of a fully connected product of N outputs over K terms (fc_split.hip): W [K][N] for
+// back-substitution (back), W [N][K] forward.
+size_t fc_stream_bytes(int N, int K);
+void launch_fc_stream(const float* W, int N, int K, bool back, void* out, hipStream_t st);
+// C[M, din] (+)= A[M, dout] * W[dout, din], Ws the layer's stream
+void launch_fc_backsub(const unsigned char* Ws, const float* A, float* C, int M, int dout, int din, bool accumulate,
+                       hipStream_t st);
 // C[M, Ci*Hi*Wi] (+)= conv-transpose of A[M, Co*Ho*Wo]
 void launch_conv_backsub(const ConvGeom& g, const float* A, float* C, int M, bool accumulate,
                          hipStream_t st);
@@ -86,8 +90,8 @@ bool launch_conv_backsub_split(const ConvGeom& g, const float* A, float* C, int 
 
 // ---- forward products (adjoint and upper-bound evaluation) ----
 // C[M, dout] = G[M, din] * W^T + b  (accumulate: C += ..., bias added either way)
-void launch_fc_forward(const float* G, const float* W, const float* b, float* C, int M, int din,
-                       int dout, bool accumulate, hipStream_t st);
+void launch_fc_forward(const unsigned char* Ws, const float* G, const float* b, float* C, int M, int din, int dout,
+                       bool accumulate, hipStream_t st);
 void launch_conv_forward(const ConvGeom& g, const float* G, float* C, int M, bool accumulate,
                          hipStream_t st, const ConeClip* clip = nullptr);
 

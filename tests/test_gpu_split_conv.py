@@ -114,3 +114,52 @@ def test_split_convolution_of_infinities(geom, bf16_weights):
             assert np.array_equal(out[r] == np.inf, hit > 0) and np.array_equal(out[r] == -np.inf, hit < 0)
             assert np.all(np.isfinite(out[r][hit == 0]))
         assert np.all(np.isfinite(out[5]))
+
+
+def _fc_net(din, dout, seed):
+    rng = np.random.default_rng(seed)
+    return [{"kind": "input", "shape": (din, 1, 1)},
+            {"kind": "fc", "src": 0, "W": rng.normal(size=(dout, din)).astype(np.float32),
+             "b": rng.normal(size=dout).astype(np.float32)},
+            {"kind": "relu", "src": 1},
+            {"kind": "fc", "src": 2, "W": np.ones((2, dout), np.float32), "b": np.zeros(2, np.float32)}], rng
+
+
+FC_DIMS = [  # (din, dout): one, four and eight reduction parts, ragged steps, octets and output tiles
+    (7, 3), (32, 16), (33, 17), (100, 10), (255, 31), (256, 100), (784, 100), (2050, 130), (100, 2100),
+]
+
+
+@pytest.mark.parametrize("dims", FC_DIMS)
+def test_split_fully_connected(dims):
+    """Both kernels (a wavefront per reduction part for few rows, 128 x 128 tiles for many) against FP64,
+    element by element; a row alone, in a small and in a large batch gives the same bits."""
+    P = _P()
+    din, dout = dims
+    nodes, rng = _fc_net(din, dout, din + dout)
+    net = P.Net(nodes)
+    W64, b = nodes[1]["W"].astype(np.float64), nodes[1]["b"].astype(np.float64)
+    big = 257 * 128 if max(din, dout) <= 256 else 33 * 128 + 1   # 256 tiles or more on one side at least
+    for name, n_in, n_out in (("fc_forward", din, dout), ("fc_backsub", dout, din)):
+        x = (rng.normal(size=(big, n_in)) * 10.0 ** rng.uniform(-12, 3, size=(big, n_in))).astype(np.float32)
+        w = W64.T if name == "fc_forward" else W64
+        add = b if name == "fc_forward" else 0.0
+        outs = {}
+        for M in (1, 17, 130, big):
+            outs[M] = _run(net, name, x[:M], n_out)
+            assert np.array_equal(outs[M][:1], outs[1])
+        assert np.array_equal(outs[big][:130], outs[130])
+        ref, mag = x[:130] @ w + add, np.abs(x[:130]).astype(np.float64) @ np.abs(w) + np.abs(add)
+        assert np.all(np.abs(outs[130] - ref) <= (6 * n_in + 21) * 2.0 ** -24 * mag + 1e-37)
+        assert np.linalg.norm(outs[130] - ref) <= 2.0 ** -22 * np.linalg.norm(mag)
+        last = slice(big - 5, big)
+        assert np.all(np.abs(outs[big][last] - (x[last] @ w + add)) <=
+                      (6 * n_in + 21) * 2.0 ** -24 * (np.abs(x[last]).astype(np.float64) @ np.abs(w) + np.abs(add)) + 1e-37)
+        for offset in (1, 2):
+            assert np.array_equal(_run(net, name, x[:17], n_out, offset), outs[17])
+        y = x[:4].copy()
+        y[0, 0], y[1, n_in - 1], y[2, n_in // 2] = np.inf, -np.inf, np.nan
+        out = _run(net, name, y, n_out)
+        assert np.array_equal(out[0] == np.inf, w[0] > 0) and np.array_equal(out[0] == -np.inf, w[0] < 0)
+        assert np.array_equal(out[1] == np.inf, w[n_in - 1] < 0) and np.array_equal(out[1] == -np.inf, w[n_in - 1] > 0)
+        assert np.all(np.isnan(out[2])) and np.all(np.isfinite(out[3]))
