@@ -65,6 +65,43 @@ static void h2d(void* dst, const void* src, size_t bytes) {
     MNB_HIP(hipStreamSynchronize(stream()));
 }
 
+// Host arrays for kernels of the same call, in stream order: small ones travel in kernel arguments
+// (sources may go away at once), larger ones as h2d.  Call flush() before the first kernel that
+// reads them.  Not for data that outlives the call without a wait at its end.
+struct Push {
+    PushArgs a;
+    Push() { a.n = 0; a.off[0] = 0; }
+    ~Push() = default;
+    void add(void* dst, const void* src, size_t bytes) {
+        constexpr size_t most = 4 * 4 * PushArgs::WORDS;
+        if (bytes == 0) return;
+        if (bytes > most || bytes % 4 != 0 || ((uintptr_t)dst & 3) != 0) {
+            h2d(dst, src, bytes);
+            return;
+        }
+        size_t done = 0, words = bytes / 4;
+        while (done < words) {
+            if (a.n == PushArgs::MAX || a.off[a.n] == PushArgs::WORDS) flush();
+            const size_t take = std::min(words - done, (size_t)(PushArgs::WORDS - a.off[a.n]));
+            memcpy(a.word + a.off[a.n], (const uint32_t*)src + done, take * 4);
+            a.dst[a.n] = (uint32_t*)dst + done;
+            a.off[a.n + 1] = a.off[a.n] + (int)take;
+            ++a.n;
+            done += take;
+        }
+    }
+    void flush() {
+        launch_push(a, stream());
+        a.n = 0;
+        a.off[0] = 0;
+    }
+};
+static void push(void* dst, const void* src, size_t bytes) {
+    Push p;
+    p.add(dst, src, bytes);
+    p.flush();
+}
+
 template <class T>
 static T* upload(const T* h, size_t n, std::vector<void*>* owned) {
     T* d = (T*)dalloc(std::max<size_t>(n * sizeof(T), 16));
@@ -1436,8 +1473,10 @@ struct Evaluator {
             const std::string tg = std::to_string((long)ch.inst_d);
             c.sh_rows_d = ws.get<RowDesc>("shr" + tg, n);
             c.sh_inst_d = ws.get<InstDesc>("shi" + tg, n);
-            h2d(c.sh_rows_d, rd.data(), n * sizeof(RowDesc));
-            h2d(c.sh_inst_d, id.data(), n * sizeof(InstDesc));
+            Push up;
+            up.add(c.sh_rows_d, rd.data(), n * sizeof(RowDesc));
+            up.add(c.sh_inst_d, id.data(), n * sizeof(InstDesc));
+            up.flush();
         }
         PassChunk sc;
         sc.M = n;
@@ -1754,7 +1793,7 @@ struct Evaluator {
                     hv.insert(hv.end(), c.bchunk_r1.begin(), c.bchunk_r1.end());
                     hv.insert(hv.end(), c.bchunk_first.begin(), c.bchunk_first.end());
                     hv.insert(hv.end(), c.bchunk_last.begin(), c.bchunk_last.end());
-                    h2d(dv, hv.data(), hv.size() * 4);
+                    push(dv, hv.data(), hv.size() * 4);
                     c.bchunk_d = dv;
                 }
                 const int nc = (int)ch.bchunk_inst.size();

@@ -279,6 +279,19 @@ void launch_spec_dot(const float* logits, int n_out, const RowDesc* rows, const 
 void launch_spec_fold(const float* C, const float* c0, const float* W, const float* b, int S, int n_out, int din,
                       float* Chat, float* chat, hipStream_t st);
 void launch_fill(float* p, long n, float v, hipStream_t st);
+struct FillArgs {   // up to eight arrays in one launch
+    int n;
+    float* p[8];
+    long count[8];
+    float v[8];
+    void add(float* q, long c, float value) {
+        if (c <= 0) return;
+        p[n] = q;
+        count[n] = c;
+        v[n++] = value;
+    }
+};
+void launch_fill(const FillArgs& a, hipStream_t st);
 void launch_heuristic_alpha(const float* l, const float* u, long ld_state, int off, int d, float* alpha,
                             long ld_param, int n_sets, int slot, hipStream_t st);
 void launch_count_unstable(const int32_t* slots, int nb, const float* l, const float* u, long ld_state, int off,
@@ -304,8 +317,29 @@ void launch_cone_zero(const PatchGeom& gc, const RowDesc* rows, int M, float* Gd
 // dense rows out[r] = shared[instance of r] + (window entries of win[r], nullable)
 void launch_patch_expand(const float* shared, const float* win, const RowDesc* rows, int M, int inst_base,
                          const PatchGeom& g, float* out, hipStream_t st);
-void launch_copy_slots(const int32_t* src, const int32_t* dst, int n, void* base, long bytes_per_slot,
-                       hipStream_t st);
+// per-slot arrays copied from src to dst slots: base, bytes per slot (word: set by the launch)
+struct SlotArrays {
+    int n;
+    char* base[8];
+    long bytes[8];
+    int word[8];
+    void add(void* p, long bytes_per_slot) {
+        if (bytes_per_slot <= 0) return;
+        base[n] = (char*)p;
+        bytes[n++] = bytes_per_slot;
+    }
+};
+void launch_copy_slots(const int32_t* src, const int32_t* dst, int n, SlotArrays a, hipStream_t st);
+// 4-byte words off[t] .. off[t + 1] - 1 of the argument to dst[t]
+struct PushArgs {
+    static constexpr int MAX = 8, WORDS = 896;
+    int n;
+    int off[MAX + 1];
+    uint32_t* dst[MAX];
+    uint32_t word[WORDS];
+};
+static_assert(sizeof(PushArgs) <= 4000, "kernel arguments");
+void launch_push(const PushArgs& a, hipStream_t st);
 void launch_apply_split(const int32_t* child, const int32_t* off_j, const int32_t* sign, int n, float* l, float* u,
                         int8_t* S, long ld_state, float* beta, long ld_param, int n_sets, hipStream_t st);
 

@@ -899,6 +899,17 @@ void launch_fill(float* p, long n, float v, hipStream_t st) {
     hipLaunchKernelGGL(k_fill, dim3(cdiv(n, 256)), dim3(256), 0, st, p, n, v);
     MNB_HIP(hipGetLastError());
 }
+__global__ __launch_bounds__(256) void k_fill_several(FillArgs a) {
+    const int t = blockIdx.y;
+    for (long j = (long)blockIdx.x * 256 + threadIdx.x; j < a.count[t]; j += (long)gridDim.x * 256) a.p[t][j] = a.v[t];
+}
+void launch_fill(const FillArgs& a, hipStream_t st) {
+    long most = 0;
+    for (int t = 0; t < a.n; ++t) most = std::max(most, a.count[t]);
+    if (most <= 0) return;
+    hipLaunchKernelGGL(k_fill_several, dim3(std::min(cdiv(most, 256), 8192), a.n), dim3(256), 0, st, a);
+    MNB_HIP(hipGetLastError());
+}
 
 // heuristic alpha (1 if u > -l else 0) for every set of a slot over one layer
 __global__ void k_heuristic_alpha(const float* l, const float* u, long ld_state, int off, int d, float* alpha,
@@ -1004,31 +1015,51 @@ void launch_build_rows(const int32_t* bs, int nk, const int32_t* slots, const in
 }
 
 // ------------------------------------------------------------------ branch_split
-// Copy per-slot arrays of the parents into the children (vector width chosen by alignment).
-template <class T>
-__global__ void k_copy_slots(const int32_t* src, const int32_t* dst, T* base, long elems_per_slot) {
-    const int c = blockIdx.y;
-    const T* s = base + (long)src[c] * elems_per_slot;
-    T* d = base + (long)dst[c] * elems_per_slot;
-    for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < elems_per_slot; i += (long)gridDim.x * blockDim.x)
-        d[i] = s[i];
-}
-void launch_copy_slots(const int32_t* src, const int32_t* dst, int n, void* base, long bytes_per_slot,
-                       hipStream_t st) {
-    if (n <= 0 || bytes_per_slot <= 0) return;
-    if (bytes_per_slot % 16 == 0 && ((uintptr_t)base % 16) == 0) {
-        long e = bytes_per_slot / 16;
-        int gx = std::min(64, cdiv(e, 256));
-        hipLaunchKernelGGL(k_copy_slots<int4>, dim3(gx, n), dim3(256), 0, st, src, dst, (int4*)base, e);
-    } else if (bytes_per_slot % 4 == 0 && ((uintptr_t)base % 4) == 0) {
-        long e = bytes_per_slot / 4;
-        int gx = std::min(64, cdiv(e, 256));
-        hipLaunchKernelGGL(k_copy_slots<int>, dim3(gx, n), dim3(256), 0, st, src, dst, (int*)base, e);
+// Copy the per-slot arrays of the parents into the children, all arrays in one launch (an array a
+// grid row: a launch each took longer than the copies on small nets), in the widest words that each
+// array's stride and address allow.
+__global__ __launch_bounds__(256) void k_copy_slots(const int32_t* src, const int32_t* dst, SlotArrays a) {
+    const int c = blockIdx.y, t = blockIdx.z;
+    const long n = a.bytes[t];
+    const char* s = a.base[t] + (long)src[c] * n;
+    char* d = a.base[t] + (long)dst[c] * n;
+    const long i0 = (long)blockIdx.x * 256 + threadIdx.x, step = (long)gridDim.x * 256;
+    if (a.word[t] == 16) {
+        for (long i = i0; i < n / 16; i += step) reinterpret_cast<int4*>(d)[i] = reinterpret_cast<const int4*>(s)[i];
+    } else if (a.word[t] == 4) {
+        for (long i = i0; i < n / 4; i += step) reinterpret_cast<int*>(d)[i] = reinterpret_cast<const int*>(s)[i];
     } else {
-        long e = bytes_per_slot;
-        int gx = std::min(64, cdiv(e, 256));
-        hipLaunchKernelGGL(k_copy_slots<char>, dim3(gx, n), dim3(256), 0, st, src, dst, (char*)base, e);
+        for (long i = i0; i < n; i += step) d[i] = s[i];
     }
+}
+void launch_copy_slots(const int32_t* src, const int32_t* dst, int n, SlotArrays a, hipStream_t st) {
+    if (n <= 0 || a.n <= 0) return;
+    long most = 1;
+    for (int t = 0; t < a.n; ++t) {
+        const uintptr_t at = (uintptr_t)a.base[t] | (uintptr_t)a.bytes[t];
+        a.word[t] = at % 16 == 0 ? 16 : at % 4 == 0 ? 4 : 1;
+        most = std::max(most, a.bytes[t] / a.word[t]);
+    }
+    const int gx = std::min(64, cdiv(most, 256));
+    for (int c = 0; c < n; c += kMaxGridY) {
+        hipLaunchKernelGGL(k_copy_slots, dim3(gx, std::min(n - c, kMaxGridY), a.n), dim3(256), 0, st, src + c, dst + c, a);
+        MNB_HIP(hipGetLastError());
+    }
+}
+
+// Small host arrays carried to the device in the kernel arguments: unlike a copy from pageable memory
+// nothing has to wait until the source is read, so the host goes on (a copy and the wait for it took
+// 20 us each, fifteen times in one small bound_optimize).
+__global__ __launch_bounds__(256) void k_push(PushArgs a) {
+    for (int i = threadIdx.x; i < a.off[a.n]; i += 256) {
+        int t = 0;
+        while (i >= a.off[t + 1]) ++t;
+        a.dst[t][i - a.off[t]] = a.word[i];
+    }
+}
+void launch_push(const PushArgs& a, hipStream_t st) {
+    if (a.n <= 0) return;
+    hipLaunchKernelGGL(k_push, dim3(1), dim3(256), 0, st, a);
     MNB_HIP(hipGetLastError());
 }
 
