@@ -976,6 +976,7 @@ struct PassCtx {
     float* cpart; int ldcp;
     int ncp = 0;
     std::map<int, float*> ap; // relu node -> a' rows [M, d] (nullable)
+    bool ap_packed = false;   // of unstable neurons only (packed_rank)
     float* G0 = nullptr;      // [M, d0]
     uint8_t* xbits = nullptr; // [M, d0]
     // gamma projections per relu layer: v, vhat [n_inst, d], gp [n_inst]
@@ -1094,6 +1095,7 @@ static void walk_backsub(PassCtx& cx, const PassChunk& ch, BufPool& pool, std::m
                 fa.inst = ch.inst_d; fa.n_inst = (int)ch.inst.size();
                 fa.slots = cx.slots_d;
                 fa.M = M; fa.d = nd.size;
+                fa.ap_packed = cx.ap_packed;
                 fa.max_rows = ch.max_rows();
                 fa.l = pb->l + net->relu_off[m]; fa.u = pb->u + net->relu_off[m];
                 fa.S = pb->S_ + net->relu_off[m]; fa.ld_state = pb->ld_state;
@@ -1317,6 +1319,7 @@ static void run_adjoint(PassCtx& cx, const PassChunk& ch, BufPool& pool, float* 
                 const bool mnc = pb->has_mnc;
                 ra.gsum_hat = mnc ? gs_hat : nullptr;
                 ra.gsum_out = mnc ? gs_out : nullptr;
+                ra.ap_packed = cx.ap_packed;
                 ra.n_slices = relax_slices(nd.size, n_inst, ch.max_rows());
                 if (ra.n_slices > 1)
                     ra.part = cx.ws->get<float>("relax_part", (size_t)ra.n_slices * n_inst * 3 * nd.size);
@@ -1643,6 +1646,8 @@ struct Evaluator {
         // receptive-field rows keep the deviation windows of a' (no checkpoints)
         cx.ckpt_stride = (adjoint && !keep_ap && ckpt_stride > 1 && !ch.pp) ? ckpt_stride : 1;
         const bool want_ap = (adjoint || keep_ap) && cx.ckpt_stride == 1;
+        // (branching scores and receptive-field rows read whole rows of a')
+        cx.ap_packed = adjoint && !keep_ap && !ch.pp;
         if (want_ap)
             for (int i : net->relus)
                 if (i <= top) {

@@ -124,6 +124,22 @@ __device__ __forceinline__ NeuronRelax neuron_relax(float l, float u, int s, flo
     return r;
 }
 
+// Packed a' rows.  The adjoint reads a' of unstable neurons only (a stable or split neuron's slope does
+// not depend on it), a tenth to a fifth of a layer, so a row keeps those alone: block b's (neurons
+// 256 b ..) sit one after the other from element 256 b on.  The fold and the relaxation map threads to
+// neurons alike and find the same places, from bounds and splits that stay as they are between the two.
+// Place of this thread's neuron in its block (valid where `unstable`); every thread of the 256 calls it.
+__device__ __forceinline__ int packed_rank(bool unstable) {
+    __shared__ int cnt[4];
+    const unsigned long long m = __ballot(unstable);
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    if (lane == 0) cnt[w] = __popcll(m);
+    __syncthreads();
+    int at = __popcll(m & ((1ull << lane) - 1));
+    for (int i = 0; i < w; ++i) at += cnt[i];
+    return at;
+}
+
 // ---- elementwise / reduction kernels (relu.hip) ----
 // Receptive-field ("patch") rows: on one node of a pass, every row is the window [C][P][P] of
 // the node that its objective neuron j sees, with origin (y_j S - Q, x_j S - Q), where (y_j, x_j)
@@ -161,6 +177,7 @@ struct FoldArgs {
     // (nullable) receives that table from a fold of the shared rows (one row per instance)
     const float4* rt_in;
     float4* rt_out;
+    int ap_packed;        // Ap holds each 256-neuron block's unstable neurons only (see packed_rank)
     int max_rows;         // most rows of an instance
     int slice_rows;       // set by the launch
 };
@@ -174,6 +191,7 @@ struct RelaxArgs {
     int M, d;
     const float* l; const float* u; const int8_t* S; long ld_state;
     const float* alpha; long ld_param; int n_sets;
+    int ap_packed;
     // gradient outputs per instance [n_inst, ldg] at column offset goff
     float* d_alpha; float* d_beta; long ldg; long goff;
     float* gsum_hat; float* gsum_out;  // nullable, [n_inst, d] (for gamma)

@@ -27,6 +27,13 @@ __global__ __launch_bounds__(256) void k_relu_fold(FoldArgs a, const float* gp) 
     const float vh = a.vhat ? a.vhat[(long)blockIdx.y * a.d + jj] : 0.f;
     const float add = (s != 0 ? (float)s * a.beta[po] : 0.f) + vh;
     const float bias = a.bias[jj];
+    // where this neuron's a' goes in a row (-1: nowhere)
+    int ap_at = ok ? j : -1;
+    if (a.ap_packed) {
+        const int at = packed_rank(ok && nr.unstable);
+        ap_at = ok && nr.unstable ? blockIdx.x * 256 + at : -1;
+    }
+    if (!a.Ap) ap_at = -1;
     const float gpv = (gp && blockIdx.x == 0 && threadIdx.x == 0) ? gp[blockIdx.y] : 0.f;
     const int col = a.col_off + blockIdx.x * 4 + (threadIdx.x >> 6);
     // the per-neuron values above complete, in a form the compiler sees: otherwise it waits for
@@ -105,7 +112,7 @@ __global__ __launch_bounds__(256) void k_relu_fold(FoldArgs a, const float* gp) 
                 const float D = neg ? nr.dneg : nr.dpos;
                 const float ah = ap * D + add;
                 a.A[e] = ah;
-                if (a.Ap) a.Ap[e] = ap;
+                if (ap_at >= 0) a.Ap[(long)r * a.d + ap_at] = ap;
                 if (a.rt_out) a.rt_out[(long)blockIdx.y * a.d + j] = make_float4(nr.dpos, nr.dneg, nr.bneg, ap);
                 contrib = (neg ? ap * nr.bneg : 0.f) + ah * bias;
             }
@@ -143,12 +150,16 @@ void launch_relu_fold(const FoldArgs& a, hipStream_t st) { launch_relu_fold(a, s
 template <bool SLICED>
 __global__ __launch_bounds__(256) void k_relu_relax(RelaxArgs a) {
     const InstDesc in = a.inst[blockIdx.y];
-    const int j = blockIdx.x * 256 + threadIdx.x;
-    if (j >= a.d) return;
+    const int j0 = blockIdx.x * 256 + threadIdx.x, j = min(j0, a.d - 1);
     const long so = (long)in.slot * a.ld_state + j;
     const long po = ((long)in.slot * a.n_sets + in.set) * a.ld_param + j;
     const int s = (int)a.S[so];
     NeuronRelax nr = neuron_relax(a.l[so], a.u[so], s, a.alpha[po]);
+    // (a neuron without a packed a' reads the place its successor has, at most its own: the value is not
+    // used, and no load stands under a condition)
+    int ap_at = j;
+    if (a.ap_packed) ap_at = blockIdx.x * 256 + packed_rank(j0 < a.d && nr.unstable);
+    if (j0 >= a.d) return;
     float da = 0.f, sh = 0.f, sg = 0.f;
     const int first = SLICED ? in.r0 + (int)blockIdx.z * kRowSlice : in.r0;
     const int last = SLICED ? min(first + kRowSlice, in.r1) : in.r1;
@@ -161,9 +172,9 @@ __global__ __launch_bounds__(256) void k_relu_relax(RelaxArgs a) {
             float ghv[RR], apv[RR];
 #pragma unroll
             for (int u = 0; u < RR; ++u) {
-                const long e = (long)min(r0 + u, z1 - 1) * a.d + j;
-                ghv[u] = a.G[e];
-                apv[u] = a.Ap[e];
+                const long row = (long)min(r0 + u, z1 - 1) * a.d;
+                ghv[u] = a.G[row + j];
+                apv[u] = a.Ap[row + ap_at];
             }
 #pragma unroll
             for (int u = 0; u < RR; ++u) {
