@@ -134,7 +134,7 @@ __global__ __launch_bounds__(64 * WN * WM, (FN * FM * NP >= 8 ? 2 : 3)) void k_c
     // 186 / 193; 4x4 / 2 into 64 channels 187 / 177, into 32 127 / 127; 3x3 / 2 114 / 108 and 89 / 91;
     // transposed 4x4 / 2 115 / 120, 121 / 95, 156 / 133, transposed 3x3 / 2 91 / 98
     constexpr bool AHEAD = NP == 2 ? PT::cnt(0) == 2 && PT::cnt(1) == 2
-                           : S == 1 ? FM <= 2 : PT::cnt(0) > 1 && FN * WN >= 4;
+                           : S == 1 ? FM <= 2 : PT::cnt(0) > 1 && (FN * WN >= 4 || (PT::cnt(0) == 4 && FN == 2 && FM == 4));
     extern __shared__ unsigned char sm[];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave % WM, wn = wave / WM;
@@ -283,7 +283,6 @@ __global__ __launch_bounds__(64 * WN * WM, (FN * FM * NP >= 8 ? 2 : 3)) void k_c
         for (int j = 0; j < FN; ++j)
 #pragma unroll
             for (int i = 0; i < FM; ++i) acc[f][j][i] += low[f][j][i];
-    const float sgn = a.ng & 1 ? -1.f : 1.f;   // the accumulators change sign once a stage
     if constexpr (NP == 1) {
         // result lanes: filter 16 j + lane % 16, positions 4 (lane / 16) + v of fragment i, which go
         // out as one 16-byte store where they are consecutive and aligned
@@ -305,7 +304,7 @@ __global__ __launch_bounds__(64 * WN * WM, (FN * FM * NP >= 8 ? 2 : 3)) void k_c
                 for (int j = 0; j < FN; ++j) {
                     floatx4 t;
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) t[v] = zero[v] ? 0.f : sgn * acc[0][j][i][v] + bias[j];
+                    for (int v = 0; v < 4; ++v) t[v] = zero[v] ? 0.f : acc[0][j][i][v] + bias[j];
                     floatx4* o4 = reinterpret_cast<floatx4*>(o + (long)j * 16 * oHW);
                     if (a.acc) t += *o4;
                     *o4 = t;
@@ -321,7 +320,7 @@ __global__ __launch_bounds__(64 * WN * WM, (FN * FM * NP >= 8 ? 2 : 3)) void k_c
                     float* o = Cl + (long)(r0 + rv) * a.ldC + pv;
 #pragma unroll
                     for (int j = 0; j < FN; ++j) {
-                        float t = zero ? 0.f : sgn * acc[0][j][i][v] + bias[j];
+                        float t = zero ? 0.f : acc[0][j][i][v] + bias[j];
                         float* o1 = o + (long)j * 16 * oHW;
                         if (a.acc) t += *o1;
                         *o1 = t;
@@ -352,7 +351,7 @@ __global__ __launch_bounds__(64 * WN * WM, (FN * FM * NP >= 8 ? 2 : 3)) void k_c
 #pragma unroll
                     for (int v = 0; v < 4; ++v) {
                         float* o2 = o + (long)(j * 16 + v) * oHW;
-                        floatx2 t = {sgn * acc[pa * 2][j][i][v], sgn * acc[pa * 2 + 1][j][i][v]};
+                        floatx2 t = {acc[pa * 2][j][i][v], acc[pa * 2 + 1][j][i][v]};
                         if (a.quad) {
                             if (a.acc) t += *reinterpret_cast<floatx2*>(o2);
                             *reinterpret_cast<floatx2*>(o2) = t;
@@ -390,7 +389,8 @@ __global__ __launch_bounds__(256) void k_split_stream(StreamArgs a, long n) {
     if (tap >= 0 && f < a.Cout && c < a.Cin) {
         const long o = a.back ? (long)c * a.Cout + f : (long)f * a.Cin + c;
         w = a.W[(o * a.k + (tap >> 8)) * a.k + (tap & 255)];
-        if ((g & 1) != (int)(a.late >> t & 1)) w = -w;
+        // the accumulators change sign once a stage, and end with the sign of the sum
+        if (((a.ng - g) & 1) != (int)(a.late >> t & 1)) w = -w;
     }
     unsigned short* dst = a.out + rest * (STEPB / 2) + lane * 8 + j;
     split_weight(w, dst);
@@ -481,7 +481,11 @@ Shape shape_of(const View& v, int pat, int pad, int cgs, const Tile& t) {
     Shape s;
     const int P = v.Ho * v.Wo, S = pat_s(pat), nd = pat_nd(pat), BM = t.BM();
     s.RS = std::max(S * (v.Wo - 1) + nd, pad + v.Wi);
-    auto lds = [&](int rows) { return ((size_t)cgs * rows * s.WH * s.RS + 1) * POSB; };
+    // positions per channel group, 1 mod 16: the groups that the lanes of a fragment read then start 48
+    // bytes apart modulo the banks, like its neighbouring positions (at 64 bytes, 108 positions, 43% of the
+    // LDS cycles were conflicts)
+    auto planes = [&](int rows) { return cgs == 1 ? rows * s.WH * s.RS : (rows * s.WH * s.RS + 14) / 16 * 16 + 1; };
+    auto lds = [&](int rows) { return ((size_t)cgs * planes(rows) + 1) * POSB; };
     if (P <= BM) {
         s.mtiles = 1;
         s.WH = S * (v.Ho - 1) + nd;
@@ -498,7 +502,7 @@ Shape shape_of(const View& v, int pat, int pad, int cgs, const Tile& t) {
         }
         s.fill = (double)P / ((double)s.mtiles * BM);
     }
-    s.plane = s.R * s.WH * s.RS;
+    s.plane = planes(s.R);
     s.lds = lds(s.R);
     return s;
 }
@@ -552,7 +556,10 @@ bool launch_split(const ConvGeom& g, const SplitConv& sc, bool back, const float
     for (int i = 0; i < nt; ++i) {
         const Shape s = shape_of(v, sc.pat, sc.pad, sc.cgs, ts[i]);
         if (s.lds > SPLIT_LDS_MAX) continue;
-        const double q = s.fill * (i == 0 ? 1.0 : 0.8);
+        // (4x4 / 2 into 32 channels on whole 256-position grids: four fragments a wavefront, 139 against 128
+        // TFLOP/s at 32x32x32)
+        const bool wide = sc.pat == PAT_F42 && ts[i].WN == 1 && ts[i].FM == 4 && v.Ho * v.Wo >= 256;
+        const double q = s.fill * (wide ? 1.05 : i == 0 ? 1.0 : 0.8);
         if (q > score) { score = q; best = i; sh = s; }
     }
     if (best < 0) return false;
