@@ -33,9 +33,11 @@
 // An output sums its stages, window offsets and part products in an order fixed by the layer, whatever
 // the batch and tile: a row's result does not depend on the rows around it.
 //
-// What bounds it: 2048 rows of 32x16x16 -> 64 (3x3) take 98 us (198 TFLOP/s; 207 us on the FP32
-// instructions before); without its global loads and stores the kernel takes 75 us, with them alone 40.
-// 32x32x32 -> 32x16x16 (4x4 / 2): 134 us against 203 at 2.5 TB/s, back 142 us against 225.
+// What bounds it, by its counters: the matrix units are busy 42 to 59 % of the time; the rest is the cutting
+// and writing of the window between two barriers and, at 4x4 / 2, the wait for the input itself.  2048
+// rows of 32x16x16 -> 64 (3x3) take 100 us (190 TFLOP/s; 207 us on the FP32 instructions before); without
+// its global loads and stores the kernel takes 75 us, with them alone 40.  32x32x32 -> 32x16x16 (4x4 / 2):
+// 125 us against 203 before at 2.7 TB/s, back 142 us against 225.
 #include "kernels.h"
 #include "split.h"
 #include "../../include/mnbab.h"
@@ -43,7 +45,8 @@
 namespace mnb {
 namespace {
 
-constexpr size_t SPLIT_LDS_MAX = 80 * 1024;
+constexpr size_t SPLIT_LDS_MAX = 64 * 1024;    // of a workgroup's window
+constexpr size_t SPLIT_LDS_ROWS = 40 * 1024;   // ... while it takes several rows: four workgroups a CU
 
 struct SplitArgs {
     const float* G; float* C; const unsigned char* Ws; const float* bias;
@@ -490,7 +493,7 @@ Shape shape_of(const View& v, int pat, int pad, int cgs, const Tile& t) {
         s.mtiles = 1;
         s.WH = S * (v.Ho - 1) + nd;
         s.R = BM / P;
-        while (s.R > 1 && lds(s.R) > SPLIT_LDS_MAX / 2) --s.R;
+        while (s.R > 1 && lds(s.R) > SPLIT_LDS_ROWS) --s.R;
         s.fill = (double)s.R * P / BM;
     } else {
         s.R = 1;

@@ -6,10 +6,12 @@
 // length alone); each part has its own accumulators and the parts' sums are added in order.  So the two
 // kernels below give the same bits, and a row's result does not depend on the batch:
 //
-// k_fc_tile, for many rows: 128 rows x 64 outputs per workgroup of four wavefronts, the parts one after
+// k_fc_tile, for many rows: 128 rows x 128 outputs per workgroup of eight wavefronts, the parts one after
 // the other.  The rows are cut into parts once per workgroup and step on their way into LDS (a row's
 // eight terms and three parts in 48 consecutive bytes, double-buffered); the filters come from their
-// stream, laid out in the order the wavefronts read it.
+// stream, laid out in the order the wavefronts read it.  The cutting is as long as the matrix work that
+// follows from it, so it has no branch and its instructions are interleaved with the matrix ones.
+// 9216 rows of 4096 -> 512 back: 254 us (152 TFLOP/s), 391 us on the FP32 instructions before.
 //
 // k_fc_parts, for few: a wavefront per part and 16 rows x 32 outputs per workgroup, operands straight
 // into registers, one exchange through LDS at the end.  A layer of few rows was a chain of K / 16 loads
@@ -97,10 +99,9 @@ __global__ __launch_bounds__(512, 2) void k_fc_tile(FcArgs a) {
     const int sr = tid >> 2, sk = tid & 3;
     const int dst = sk * PLANE + sr * POSB;
     float x[2][8];   // the next step's octet and the one after it
-    auto stage = [&](int k, int b, float* v) {
-        mask8(a, k, k * 32 + sk * 8, v);
+    auto stage = [&](int b, const float* v) {
         uintx4 p0, p1, p2;
-        split8(v, p0, p1, p2);
+        split8_clamped(v, p0, p1, p2);
         unsigned char* d = sm + b * BUF + dst;
         *reinterpret_cast<uintx4*>(d) = p0;
         *reinterpret_cast<uintx4*>(d + 16) = p1;
@@ -113,7 +114,9 @@ __global__ __launch_bounds__(512, 2) void k_fc_tile(FcArgs a) {
 #pragma unroll
         for (int s = 0; s < 3; ++s) wb[0][j][s] = *reinterpret_cast<const bf16x8*>(wp[j] + s * 1024 + lo16);
     load8(a, m0 + sr, 32 + sk * 8, x[1]);
-    stage(0, 0, x[0]);
+    mask8(a, 0, sk * 8, x[0]);
+    mask8(a, 1, 32 + sk * 8, x[1]);
+    stage(0, x[0]);
     __syncthreads();
 
     floatx4 hi[FN][FM], low[FN][FM], sum[FN][FM];
@@ -139,7 +142,7 @@ __global__ __launch_bounds__(512, 2) void k_fc_tile(FcArgs a) {
         for (int i = 0; i < FM; ++i)
 #pragma unroll
             for (int s = 0; s < 3; ++s) rf[i][s] = *reinterpret_cast<const bf16x8*>(buf + i * 16 * POSB + s * 16);
-        stage(k + 1, b ^ 1, x[b ^ 1]);
+        stage(b ^ 1, x[b ^ 1]);
 #pragma unroll
         for (int i = 0; i < FM; ++i) MNB_SPLIT_MM(FN, wb[b], rf[i], hi, low, i)
         // one matrix instruction, then up to three vector ones in its shadow
@@ -148,6 +151,7 @@ __global__ __launch_bounds__(512, 2) void k_fc_tile(FcArgs a) {
             __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
             __builtin_amdgcn_sched_group_barrier(0x002, 3, 0);
         }
+        mask8(a, k + 2, (k + 2) * 32 + sk * 8, x[b]);   // (waits for the rows only where K ends)
         if (k + 1 == half) {
 #pragma unroll
             for (int j = 0; j < FN; ++j)

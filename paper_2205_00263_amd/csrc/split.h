@@ -44,6 +44,27 @@ __device__ __forceinline__ void split8(const float* x, uintx4& h, uintx4& m, uin
     }
 }
 
+// The same without a branch, for matrix instructions that are scheduled among these: the first two parts
+// are clamped to the largest bf16 instead, so that no finite value rounds up to an infinity, and an
+// infinity (NaN) ends up in the third part, behind two finite ones of its sign.  Twelve more instructions
+// an octet: the convolutions, which stage between their stages, are 5 to 9 % slower with it.
+__device__ __forceinline__ void split8_clamped(const float* x, uintx4& h, uintx4& m, uintx4& l) {
+    constexpr float top = 3.38953139e38f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const floatx2 v = {x[2 * i], x[2 * i + 1]};
+        const floatx2 vc = {__builtin_amdgcn_fmed3f(v[0], -top, top), __builtin_amdgcn_fmed3f(v[1], -top, top)};
+        const unsigned p = __builtin_bit_cast(unsigned, __builtin_convertvector(vc, bf16x2));
+        const floatx2 r = {v[0] - __uint_as_float(p << 16), v[1] - __uint_as_float(p & 0xffff0000u)};
+        const floatx2 rc = {__builtin_amdgcn_fmed3f(r[0], -top, top), __builtin_amdgcn_fmed3f(r[1], -top, top)};
+        const unsigned q = __builtin_bit_cast(unsigned, __builtin_convertvector(rc, bf16x2));
+        const floatx2 t = {r[0] - __uint_as_float(q << 16), r[1] - __uint_as_float(q & 0xffff0000u)};
+        h[i] = p;
+        m[i] = q;
+        l[i] = __builtin_bit_cast(unsigned, __builtin_convertvector(t, bf16x2));
+    }
+}
+
 // The parts of a filter weight, cut off (each part has the sign of the weight), to dst, dst + 512 and
 // dst + 1024.  A part of a nonzero weight is never zero (the smallest normal instead), so that an
 // infinite operand gives the infinity an FP32 product gives and no 0 x inf.
