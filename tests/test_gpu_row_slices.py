@@ -102,3 +102,21 @@ def test_objective_rows_from_filters_of_a_sum(filter_first):
              {"kind": "add", "src": 5 if filter_first else 6, "src2": 6 if filter_first else 5},
              {"kind": "relu", "src": 7}, _fc(rng, 8, 45, 3)]
     _check(nodes, 36, 7, 0.3)
+
+
+@pytest.mark.parametrize("n", [1, 223, 224, 225, 448, 449, 897, 1793])
+def test_uploads_of_every_length(n):
+    """Lists of n splits and 2 n subproblems around the lengths that travel in one kernel's arguments
+    (896 words), in several (3584) and by a copy: equal splits of one parent have equal bounds."""
+    import paper_2205_00263_amd as P
+    rng = np.random.default_rng(3)
+    nodes = [{"kind": "input", "shape": (6, 1, 1)}, _fc(rng, 0, 6, 24), {"kind": "relu", "src": 1},
+             _fc(rng, 2, 24, 9), {"kind": "relu", "src": 3}, _fc(rng, 4, 9, 3)]
+    x = rng.normal(size=6)
+    pb = P.Problem(P.Net(nodes), n_spec=2, capacity=2 * n + 24)
+    rid, _, _ = pb.bound_init(x - 0.5, x + 0.5, rng.normal(size=(2, 3)), np.zeros(2))
+    W1 = nodes[1]["W"].astype(np.float64)
+    few = np.nonzero(np.abs(W1 @ x + nodes[1]["b"]) < 0.4 * np.abs(W1).sum(1))[0][:4]   # unstable
+    alone = np.array([pb.bound_optimize(pb.branch_split([rid], [0], [int(j)]), steps=0)[0] for j in few])
+    lb, _ = pb.bound_optimize(pb.branch_split([rid] * n, [0] * n, few[np.arange(n) % len(few)]), steps=0)
+    assert np.array_equal(lb.reshape(n, 2, -1), alone[np.arange(n) % len(few)])
