@@ -56,67 +56,22 @@ void launch_init_conv_patch(const RowDesc* rows, int M, const float* W, const fl
 }
 
 // ------------------------------------------------------------------ fold (Eq. 5) of deviation windows
-// One workgroup per (row, 256 window entries).  With U' the shared row's a' and d the row's
+// One wavefront per (row, 256 window entries).  With U' the shared row's a' and d the row's
 // deviation, the row's a' is U' + d; the deviation of ahat is (U' + d) D(U' + d) - U' D(U') (the
 // set's S beta + Phat^T gamma cancel), the deviation of the row constant
 // (U' + d) b(U' + d) - U' b(U') + dev(ahat) . bias; gamma . p is in the shared row's constant.
 // Where both sides select the same slope the deviation is formed as d D (no cancellation).
-__global__ __launch_bounds__(256) void k_relu_fold_patch(FoldArgs a, PatchGeom g, const RowDesc* rows, int inst_base,
-                                                         int nblk) {
+// A lane takes the entries 64 apart, all their loads in flight together: the 16-byte table entries of
+// neighbouring lanes then lie side by side in L1 lines, whose lookups bounded the kernel (four consecutive
+// entries a lane with 16-byte loads of the deviations, four times the lookups: 419 us a launch on a batch
+// of 128 ConvBig subproblems; 332 so).  Index arithmetic by float reciprocals (exact here:
+// entries and window sides are far below 2^22); the partial constants are one per 64 entries.
+__global__ __launch_bounds__(256) void k_relu_fold_patch(FoldArgs a, PatchGeom g, const RowDesc* rows,
+                                                         int inst_base, int nblk, float inv_pp, float inv_p) {
     const long bid = blockIdx.x;
     const int r = (int)(bid / nblk), eb = (int)(bid - (long)r * nblk);
-    const RowDesc rd = rows[r];
-    const int li = rd.inst - inst_base;
-    const InstDesc in = a.inst[li];
-    const int width = g.C * g.P * g.P;
-    const int e = eb * 256 + threadIdx.x;
-    const bool ok = e < width;
-    int oy, ox;
-    patch_origin(g, rd.j, oy, ox);
-    const int PP = g.P * g.P;
-    const int c = ok ? e / PP : 0;
-    const int q = ok ? e - c * PP : 0;
-    const int Y = oy + q / g.P, X = ox + q % g.P;
-    const bool inside = ok && Y >= 0 && Y < g.H && X >= 0 && X < g.W;
-    const int n = inside ? (c * g.H + Y) * g.W + X : 0;
-    (void)in;
-    float contrib = 0.f;
-    const long idx = (long)r * width + e;
-    const float dv = ok ? a.A[idx] : 0.f;
-    if (inside) {
-        const float4 t = a.rt_in[(long)li * a.d + n];   // {D(a' >= 0), D(a' < 0), b, U'}
-        const float U = t.w;
-        const float ap = U + dv;
-        const bool neg = ap < 0.f, uneg = U < 0.f;
-        float dh, dc;
-        if (neg == uneg) {
-            const float D = neg ? t.y : t.x;
-            dh = dv * D;
-            dc = neg ? dv * t.z : 0.f;
-        } else {
-            dh = ap * (neg ? t.y : t.x) - U * (uneg ? t.y : t.x);
-            dc = (neg ? ap * t.z : 0.f) - (uneg ? U * t.z : 0.f);
-        }
-        a.A[idx] = dh;
-        if (a.Ap) a.Ap[idx] = dv;
-        contrib = dc + dh * a.bias[n];
-    } else if (ok) {
-        a.A[idx] = 0.f;
-        if (a.Ap) a.Ap[idx] = 0.f;
-    }
-    contrib = wave_sum(contrib);
-    if ((threadIdx.x & 63) == 0) a.cpart[(long)r * a.ldcp + a.col_off + eb * 4 + (threadIdx.x >> 6)] = contrib;
-}
-
-// The same fold with four consecutive window entries per lane (windows of a multiple of 4 entries):
-// one wavefront per 256 entries, 16-byte loads and stores, index arithmetic by float reciprocals
-// (exact here: entries and window sides are far below 2^22), and the partial constants still one
-// per 64 entries (the sum over each 16-lane row).
-__global__ __launch_bounds__(256) void k_relu_fold_patch4(FoldArgs a, PatchGeom g, const RowDesc* rows,
-                                                          int inst_base, int nblk, float inv_pp, float inv_p) {
-    const long bid = blockIdx.x;
-    const int r = (int)(bid / nblk), eb = (int)(bid - (long)r * nblk);
-    const int lane = threadIdx.x & 63, chunk = eb * 4 + (threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+    const int chunk = __builtin_amdgcn_readfirstlane(eb * 4 + (int)(threadIdx.x >> 6));
     const int width = g.C * g.P * g.P;
     if (chunk * 256 >= width) return;   // wavefront-uniform
     const RowDesc rd = rows[r];
@@ -124,22 +79,24 @@ __global__ __launch_bounds__(256) void k_relu_fold_patch4(FoldArgs a, PatchGeom 
     int oy, ox;
     patch_origin(g, rd.j, oy, ox);
     const int PP = g.P * g.P;
-    const int e0 = chunk * 256 + 4 * lane;
-    const bool ok = e0 < width;
-    const long idx = (long)r * width + (ok ? e0 : 0);
-    const float4 dv4 = ok ? *reinterpret_cast<const float4*>(a.A + idx) : make_float4(0.f, 0.f, 0.f, 0.f);
-    const float dvs[4] = {dv4.x, dv4.y, dv4.z, dv4.w};
-    float dh[4], contrib = 0.f;
-    bool ins[4];
+    const long at = (long)r * width;
+    float dv[4];
+    bool ok[4], ins[4];
     int nn[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-        const int e = e0 + k;
+        const int e = chunk * 256 + 64 * k + lane;
+        ok[k] = e < width;
+        dv[k] = a.A[at + (ok[k] ? e : 0)];
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const int e = chunk * 256 + 64 * k + lane;
         const int c = (int)(((float)e + 0.5f) * inv_pp);
         const int q = e - c * PP;
         const int qy = (int)(((float)q + 0.5f) * inv_p);
         const int Y = oy + qy, X = ox + q - qy * g.P;
-        ins[k] = ok && Y >= 0 && Y < g.H && X >= 0 && X < g.W;
+        ins[k] = ok[k] && Y >= 0 && Y < g.H && X >= 0 && X < g.W;
         nn[k] = ins[k] ? (c * g.H + Y) * g.W + X : 0;
     }
     float4 tt[4];
@@ -149,48 +106,41 @@ __global__ __launch_bounds__(256) void k_relu_fold_patch4(FoldArgs a, PatchGeom 
         tt[k] = a.rt_in[(long)li * a.d + nn[k]];   // {D(a' >= 0), D(a' < 0), b, U'}
         bb[k] = a.bias[nn[k]];
     }
+    float dh[4], contrib[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-        dh[k] = 0.f;
-        if (!ins[k]) continue;
         const float4 t = tt[k];
-        const float U = t.w, d = dvs[k];
+        const float U = t.w, d = dv[k];
         const float ap = U + d;
         const bool neg = ap < 0.f, uneg = U < 0.f;
         float dc;
         if (neg == uneg) {
-            const float D = neg ? t.y : t.x;
-            dh[k] = d * D;
+            dh[k] = d * (neg ? t.y : t.x);
             dc = neg ? d * t.z : 0.f;
         } else {
             dh[k] = ap * (neg ? t.y : t.x) - U * (uneg ? t.y : t.x);
             dc = (neg ? ap * t.z : 0.f) - (uneg ? U * t.z : 0.f);
         }
-        contrib += dc + dh[k] * bb[k];
+        contrib[k] = ins[k] ? dc + dh[k] * bb[k] : 0.f;
     }
-    if (ok) {
-        *reinterpret_cast<float4*>(a.A + idx) = make_float4(dh[0], dh[1], dh[2], dh[3]);
-        if (a.Ap)
-            *reinterpret_cast<float4*>(a.Ap + idx) = make_float4(ins[0] ? dvs[0] : 0.f, ins[1] ? dvs[1] : 0.f,
-                                                                 ins[2] ? dvs[2] : 0.f, ins[3] ? dvs[3] : 0.f);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const int e = chunk * 256 + 64 * k + lane;
+        if (ok[k]) {
+            a.A[at + e] = ins[k] ? dh[k] : 0.f;
+            if (a.Ap) a.Ap[at + e] = ins[k] ? dv[k] : 0.f;
+        }
+        const float sum = wave_sum(contrib[k]);
+        if (lane == 63) a.cpart[(long)r * a.ldcp + a.col_off + chunk * 4 + k] = sum;
     }
-    contrib = row16_sum(contrib);
-    if ((lane & 15) == 15) a.cpart[(long)r * a.ldcp + a.col_off + chunk * 4 + (lane >> 4)] = contrib;
 }
 
 void launch_relu_fold_patch(const FoldArgs& a, const PatchGeom& g, const RowDesc* rows, int inst_base,
                             hipStream_t st) {
     if (a.M <= 0) return;
-    const int width = g.C * g.P * g.P;
-    if (width % 4 == 0 && ((uintptr_t)a.A & 15) == 0 && (!a.Ap || ((uintptr_t)a.Ap & 15) == 0)) {
-        const int nblk = cdiv(width, 1024);
-        hipLaunchKernelGGL(k_relu_fold_patch4, dim3((unsigned)((long)a.M * nblk)), dim3(256), 0, st, a, g, rows,
-                           inst_base, nblk, 1.f / (float)(g.P * g.P), 1.f / (float)g.P);
-    } else {
-        const int nblk = cdiv(width, 256);
-        hipLaunchKernelGGL(k_relu_fold_patch, dim3((unsigned)((long)a.M * nblk)), dim3(256), 0, st, a, g, rows,
-                           inst_base, nblk);
-    }
+    const int nblk = cdiv(g.C * g.P * g.P, 1024);
+    hipLaunchKernelGGL(k_relu_fold_patch, dim3((unsigned)((long)a.M * nblk)), dim3(256), 0, st, a, g, rows, inst_base,
+                       nblk, 1.f / (float)(g.P * g.P), 1.f / (float)g.P);
     MNB_HIP(hipGetLastError());
 }
 
