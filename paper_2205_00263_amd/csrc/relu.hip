@@ -967,60 +967,65 @@ void launch_count_unstable(const int32_t* slots, int nb, const float* l, const f
 // Row descriptors of an intermediate-bound pass: for local subproblem b, its
 // unstable neurons in index order, lower rows (+e_j, instance 2k) then upper
 // rows (-e_j, instance 2k+1), starting at row offset row0[b].
-__global__ void k_build_rows(const int32_t* bs, const int32_t* slots, const int32_t* row0, const int32_t* inst0,
-                             const float* l, const float* u, long ld_state, int off, int d, RowDesc* rows) {
-    const int k = blockIdx.x;
-    const int b = bs[k];
-    const int slot = slots[b];
-    const int base = row0[k];
-    __shared__ int scan[256];
-    __shared__ int carry;
-    if (threadIdx.x == 0) carry = 0;
-    __syncthreads();
-    // count of this subproblem's unstable neurons (rows per direction)
-    int total = 0;
-    for (int j = threadIdx.x; j < d; j += 256) {
-        long so = (long)slot * ld_state + off + j;
-        total += (l[so] < 0.f && u[so] > 0.f) ? 1 : 0;
+// Sixteen wavefronts count a sixteenth of the layer each, then place their own neurons by ballots: one
+// barrier in all (a scan of 256 neurons at a time took 19 barriers each: 37 us on average over the layers
+// of one ConvBig instance, 6 so).
+__global__ __launch_bounds__(1024) void k_build_rows(const int32_t* bs, const int32_t* slots, const int32_t* row0,
+                                                     const int32_t* inst0, const float* l, const float* u,
+                                                     long ld_state, int off, int d, RowDesc* rows) {
+    constexpr int NW = 16, U = 4;
+    __shared__ int count[NW];
+    const int k = blockIdx.x, lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int b = bs[k], base = row0[k], inst = inst0[k];
+    const long so = (long)slots[b] * ld_state + off;
+    const int seg = (d + 64 * NW - 1) / (64 * NW) * 64;
+    const int first = wave * seg, last = min(first + seg, d);
+    // 64 neurons' flags a word, U words' loads in flight together
+    auto flags = [&](int j0, unsigned long long* f) {
+        float lv[U], uv[U];
+#pragma unroll
+        for (int t = 0; t < U; ++t) {
+            const int j = min(j0 + 64 * t + lane, d - 1);
+            lv[t] = l[so + j];
+            uv[t] = u[so + j];
+        }
+#pragma unroll
+        for (int t = 0; t < U; ++t) f[t] = __ballot(j0 + 64 * t + lane < last && lv[t] < 0.f && uv[t] > 0.f);
+    };
+    int mine = 0;
+    for (int j0 = first; j0 < last; j0 += 64 * U) {
+        unsigned long long f[U];
+        flags(j0, f);
+#pragma unroll
+        for (int t = 0; t < U; ++t) mine += __popcll(f[t]);
     }
-    scan[threadIdx.x] = total;
+    if (lane == 0) count[wave] = mine;
     __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if (threadIdx.x < w) scan[threadIdx.x] += scan[threadIdx.x + w];
-        __syncthreads();
+    int pos = 0, nu = 0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+        if (w < wave) pos += count[w];
+        nu += count[w];
     }
-    const int nu = scan[0];
-    __syncthreads();
-    for (int j0 = 0; j0 < d; j0 += 256) {
-        const int j = j0 + threadIdx.x;
-        int flag = 0;
-        if (j < d) {
-            long so = (long)slot * ld_state + off + j;
-            flag = (l[so] < 0.f && u[so] > 0.f) ? 1 : 0;
+    for (int j0 = first; j0 < last; j0 += 64 * U) {
+        unsigned long long f[U];
+        flags(j0, f);
+#pragma unroll
+        for (int t = 0; t < U; ++t) {
+            if (f[t] >> lane & 1) {
+                const int at = base + pos + __popcll(f[t] & ((1ull << lane) - 1)), j = j0 + 64 * t + lane;
+                rows[at] = RowDesc{b, inst, j, 1};
+                rows[at + nu] = RowDesc{b, inst + 1, j, -1};
+            }
+            pos += __popcll(f[t]);
         }
-        scan[threadIdx.x] = flag;
-        __syncthreads();
-        for (int w = 1; w < 256; w <<= 1) {
-            int v = threadIdx.x >= w ? scan[threadIdx.x - w] : 0;
-            __syncthreads();
-            scan[threadIdx.x] += v;
-            __syncthreads();
-        }
-        if (flag) {
-            const int pos = carry + scan[threadIdx.x] - 1;
-            rows[base + pos] = RowDesc{b, inst0[k], j, 1};
-            rows[base + nu + pos] = RowDesc{b, inst0[k] + 1, j, -1};
-        }
-        __syncthreads();
-        if (threadIdx.x == 255) carry += scan[255];
-        __syncthreads();
     }
 }
 void launch_build_rows(const int32_t* bs, int nk, const int32_t* slots, const int32_t* row0, const int32_t* inst0,
                        const float* l, const float* u, long ld_state, int off, int d, RowDesc* rows,
                        hipStream_t st) {
     if (nk <= 0) return;
-    hipLaunchKernelGGL(k_build_rows, dim3(nk), dim3(256), 0, st, bs, slots, row0, inst0, l, u, ld_state, off, d,
+    hipLaunchKernelGGL(k_build_rows, dim3(nk), dim3(1024), 0, st, bs, slots, row0, inst0, l, u, ld_state, off, d,
                        rows);
     MNB_HIP(hipGetLastError());
 }

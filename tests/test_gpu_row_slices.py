@@ -84,6 +84,15 @@ def test_row_slices_of_fully_connected_layers(width, rows):
     assert max(used) > rows // 2   # most rows of the second layer take part
 
 
+@pytest.mark.parametrize("rows", [63, 64, 65, 1023, 1024, 1025, 2049])
+def test_rows_of_wide_layers(rows):
+    """Row lists built by sixteen wavefronts, 64 neurons at a time."""
+    rng = np.random.default_rng(rows)
+    nodes = [{"kind": "input", "shape": (8, 1, 1)}, _fc(rng, 0, 8, 30), {"kind": "relu", "src": 1},
+             _fc(rng, 2, 30, rows), {"kind": "relu", "src": 3}, _fc(rng, 4, rows, 3)]
+    _check(nodes, 8, 5, 0.6)
+
+
 @pytest.mark.parametrize("k,s,p", [(3, 1, 1), (4, 2, 1), (3, 2, 0), (2, 1, 0), (1, 2, 0)])
 def test_objective_rows_from_filters(k, s, p):
     rng = np.random.default_rng(10 * k + s)
