@@ -316,7 +316,10 @@ __global__ __launch_bounds__(64 * WN * WM, (FN * FM * NP >= 8 ? 2 : 3)) void k_c
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
                     int rv = rl, pv = pos + v;
-                    if (pv >= a.P && a.R > 1) { pv -= a.P; ++rv; }
+                    if (a.R > 1) {   // (on a grid of one position the four belong to four rows)
+                        rv = qdiv(q + v, a.rP);
+                        pv = q + v - rv * a.P;
+                    }
                     if (rv >= rows || pv >= a.P) continue;
                     bool zero = false;
                     if (a.clip.rows) zero = clipped(a, r0 + rv, pv);
