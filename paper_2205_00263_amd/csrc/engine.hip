@@ -110,6 +110,13 @@ static T* upload(const T* h, size_t n, std::vector<void*>* owned) {
     return d;
 }
 static void sync() { MNB_HIP(hipStreamSynchronize(stream())); }
+// Before memory that launched work may still use is given back on an error path.
+static void drain() noexcept {
+    try {
+        sync();
+    } catch (...) {
+    }
+}
 }  // namespace mnb
 
 // ---------------------------------------------------------------- kernel timer
@@ -679,6 +686,7 @@ extern "C" int mnb_net_create(const mnb_layer* L_in, int n_in, mnb_net** out) {
         for (int m = 0; m < (int)net->relus.size(); ++m) net->patch.push_back(make_patch_plan(net, m, conv_wh));
         sync();
     } catch (...) {
+        drain();   // (filter streams may still be written)
         delete net;
         throw;
     }

@@ -1,0 +1,106 @@
+"""Calls that fail half way: device memory goes back to the installed allocator only when nothing on the stream
+can still use it, each pointer once, and later calls work.  Runs in a process of its own, since an allocator is
+installed before any object is created."""
+import os
+import subprocess
+import sys
+
+import pytest
+
+pytestmark = pytest.mark.gpu
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+HOOKS = r"""
+import ctypes as C, sys
+sys.path.insert(0, ROOT)
+import numpy as np, torch
+import paper_2205_00263_amd as P
+from paper_2205_00263_amd import _lib
+import workloads as W
+
+stream = torch.cuda.Stream()
+live, calls, fail_at = set(), [0], [0]
+wrong = []
+
+def alloc(n, ctx):
+    calls[0] += 1
+    if calls[0] == fail_at[0]:
+        return None
+    p = int(torch.cuda.caching_allocator_alloc(int(n), 0, stream))
+    live.add(p)
+    return p
+
+def free(p, ctx):
+    if not stream.query():
+        wrong.append("freed under running work")
+    if p not in live:
+        wrong.append("freed twice")
+        return
+    live.remove(p)
+    torch.cuda.caching_allocator_delete(p)
+
+hooks = _lib.ALLOC_FN(alloc), _lib.FREE_FN(free)
+_lib.check(_lib.lib().mnb_set_allocator(hooks[0], hooks[1], None))
+_lib.check(_lib.lib().mnb_set_stream(C.c_void_p(stream.cuda_stream)))
+
+def failing(k, call):
+    # the k-th allocation of the call returns NULL; whether the call failed
+    calls[0], fail_at[0] = 0, k
+    try:
+        call()
+        return False
+    except _lib.MnbError as e:
+        assert e.code in (_lib.MNB_ENOMEM, _lib.MNB_EINVAL), e
+        return True
+    finally:
+        fail_at[0] = 0
+
+wl = W.make_workload(4, scale="small")
+"""
+
+CREATION = HOOKS + r"""
+bad = wl.nodes[:2] + [{"kind": "relu", "src": 1}, {"kind": "add", "src": 2, "src2": 1}] + [
+    {"kind": "relu", "src": 3}, {"kind": "fc", "src": 4, "W": np.ones((2, 1), np.float32), "b": np.zeros(2, np.float32)}]
+rng = np.random.default_rng(0)
+wide = [{"kind": "input", "shape": (64, 8, 8)},
+        {"kind": "conv", "src": 0, "W": rng.normal(size=(256, 64, 3, 3)).astype(np.float32), "b": np.zeros(256, np.float32),
+         "stride": 1, "pad": 1}, {"kind": "relu", "src": 1}, {"kind": "add", "src": 2, "src2": 1},
+        {"kind": "relu", "src": 3}, {"kind": "fc", "src": 4, "W": np.ones((2, 256 * 64), np.float32), "b": np.zeros(2, np.float32)}]
+for nodes in (bad, wide):
+    assert failing(0, lambda: P.Net(nodes)) and not live
+k = 1
+while failing(k, lambda: P.Net(wl.nodes)):
+    assert not live, k
+    k += 1
+import gc; gc.collect()
+assert k > 20 and not wrong, (k, wrong[:3])
+print("ok", k)
+"""
+
+SESSION = HOOKS + r"""
+net = P.Net(wl.nodes)
+pb = P.Problem(net, n_spec=wl.C.shape[0], capacity=16)
+rid, _, _ = pb.bound_init(wl.lo, wl.hi, wl.C, wl.c0)
+l, u, _ = pb.get_bounds(rid, 0)
+kids = pb.branch_split([rid], [0], [int(np.nonzero((l < 0) & (u > 0))[0][0])])
+before = set(live)
+k = 1
+while failing(k, lambda: pb.optimize_begin(kids, steps=2)):
+    assert live == before, k
+    k += 1
+assert k > 5 and not wrong, (k, wrong[:3])
+print("ok", k)
+"""
+
+
+def _run_child(script):
+    r = subprocess.run([sys.executable, "-c", "ROOT = %r\n" % ROOT + script], capture_output=True, text=True, timeout=100)
+    assert r.returncode == 0 and r.stdout.strip().splitlines()[-1].startswith("ok"), r.stdout[-2000:] + r.stderr[-4000:]
+
+
+def test_net_creation_that_fails():
+    _run_child(CREATION)
+
+
+def test_session_that_fails_to_begin():
+    _run_child(SESSION)
