@@ -32,6 +32,7 @@ struct Workspace {
             if (b.p) {
                 MNB_HIP(hipStreamSynchronize(stream()));
                 dfree(b.p);
+                b = Buf{};   // (the allocation below may fail)
             }
             size_t nb = bytes + bytes / 8 + 256;
             b.p = dalloc(nb);

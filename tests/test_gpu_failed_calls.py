@@ -44,13 +44,14 @@ _lib.check(_lib.lib().mnb_set_allocator(hooks[0], hooks[1], None))
 _lib.check(_lib.lib().mnb_set_stream(C.c_void_p(stream.cuda_stream)))
 
 def failing(k, call):
-    # the k-th allocation of the call returns NULL; whether the call failed
+    # the k-th allocation of the call returns NULL (0: none, the arguments are bad); whether the call failed
     calls[0], fail_at[0] = 0, k
     try:
         call()
         return False
     except _lib.MnbError as e:
-        assert e.code in (_lib.MNB_ENOMEM, _lib.MNB_EINVAL), e
+        assert e.code == (_lib.MNB_ENOMEM if k else _lib.MNB_EINVAL), e
+        assert k < 500
         return True
     finally:
         fail_at[0] = 0
@@ -92,6 +93,24 @@ assert k > 5 and not wrong, (k, wrong[:3])
 print("ok", k)
 """
 
+GROWTH = HOOKS + r"""
+net = P.Net(wl.nodes)
+pb = P.Problem(net, n_spec=wl.C.shape[0], capacity=16)
+rid, _, _ = pb.bound_init(wl.lo, wl.hi, wl.C, wl.c0)
+groups = lambda n: np.stack([np.arange(n), np.arange(n) + 1, np.arange(n) + 2], 1).astype(np.int32)
+want = pb.octahedral_bounds(rid, 1, groups(2)).copy()
+k = 1
+while failing(k, lambda: pb.octahedral_bounds(rid, 1, groups(28))):
+    # what the failed call had grown or lost is there again, at the smaller size too
+    assert np.array_equal(pb.octahedral_bounds(rid, 1, groups(2)), want), k
+    k += 1
+assert k > 2 and np.array_equal(pb.octahedral_bounds(rid, 1, groups(28))[:2], want)
+del pb, net
+import gc; gc.collect()
+assert not wrong and not live, (wrong[:3], len(live))
+print("ok", k)
+"""
+
 
 def _run_child(script):
     r = subprocess.run([sys.executable, "-c", "ROOT = %r\n" % ROOT + script], capture_output=True, text=True, timeout=100)
@@ -104,3 +123,7 @@ def test_net_creation_that_fails():
 
 def test_session_that_fails_to_begin():
     _run_child(SESSION)
+
+
+def test_workspace_that_fails_to_grow():
+    _run_child(GROWTH)
