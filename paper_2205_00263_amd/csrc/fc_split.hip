@@ -10,7 +10,8 @@
 // the other.  The rows are cut into parts once per workgroup and step on their way into LDS (a row's
 // eight terms and three parts in 48 consecutive bytes, double-buffered); the filters come from their
 // stream, laid out in the order the wavefronts read it.  The cutting is as long as the matrix work that
-// follows from it, so it has no branch and its instructions are interleaved with the matrix ones.
+// follows from it, so it has no branch and its instructions are interleaved with the matrix ones; octets that
+// need the branch (infinities, values that round up to one) are cut again behind them.
 // 9216 rows of 4096 -> 512 back: 254 us (152 TFLOP/s), 391 us on the FP32 instructions before.
 //
 // k_fc_parts, for few: a wavefront per part and 16 rows x 32 outputs per workgroup, operands straight
@@ -99,14 +100,13 @@ __global__ __launch_bounds__(512, 2) void k_fc_tile(FcArgs a) {
     const int sr = tid >> 2, sk = tid & 3;
     const int dst = sk * PLANE + sr * POSB;
     float x[2][8];   // the next step's octet and the one after it
-    auto stage = [&](int b, const float* v) {
-        uintx4 p0, p1, p2;
-        split8_clamped(v, p0, p1, p2);
+    auto put = [&](int b, uintx4 p0, uintx4 p1, uintx4 p2) {
         unsigned char* d = sm + b * BUF + dst;
         *reinterpret_cast<uintx4*>(d) = p0;
         *reinterpret_cast<uintx4*>(d + 16) = p1;
         *reinterpret_cast<uintx4*>(d + 32) = p2;
     };
+    uintx4 p0, p1, p2;
     load8(a, m0 + sr, sk * 8, x[0]);
     bf16x8 wb[2][FN][3];
 #pragma unroll
@@ -116,7 +116,8 @@ __global__ __launch_bounds__(512, 2) void k_fc_tile(FcArgs a) {
     load8(a, m0 + sr, 32 + sk * 8, x[1]);
     mask8(a, 0, sk * 8, x[0]);
     mask8(a, 1, 32 + sk * 8, x[1]);
-    stage(0, x[0]);
+    split8(x[0], p0, p1, p2);
+    put(0, p0, p1, p2);
     __syncthreads();
 
     floatx4 hi[FN][FM], low[FN][FM], sum[FN][FM];
@@ -142,14 +143,20 @@ __global__ __launch_bounds__(512, 2) void k_fc_tile(FcArgs a) {
         for (int i = 0; i < FM; ++i)
 #pragma unroll
             for (int s = 0; s < 3; ++s) rf[i][s] = *reinterpret_cast<const bf16x8*>(buf + i * 16 * POSB + s * 16);
-        stage(b ^ 1, x[b ^ 1]);
+        split8<false>(x[b ^ 1], p0, p1, p2);
+        put(b ^ 1, p0, p1, p2);
+        const float big = max8(x[b ^ 1]);
 #pragma unroll
         for (int i = 0; i < FM; ++i) MNB_SPLIT_MM(FN, wb[b], rf[i], hi, low, i)
-        // one matrix instruction, then up to three vector ones in its shadow
+        // one matrix instruction, then up to two vector ones in its shadow (three: 1 to 3 % slower)
 #pragma unroll
         for (int q = 0; q < 48; ++q) {
             __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            __builtin_amdgcn_sched_group_barrier(0x002, 3, 0);
+            __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);
+        }
+        if (big >= SPLIT_BIG) {   // cut again, where it is not among the matrix instructions
+            split8(x[b ^ 1], p0, p1, p2);
+            put(b ^ 1, p0, p1, p2);
         }
         mask8(a, k + 2, (k + 2) * 32 + sk * 8, x[b]);   // (waits for the rows only where K ends)
         if (k + 1 == half) {

@@ -14,50 +14,40 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 constexpr int POSB = 48;              // LDS bytes of eight staged terms: 3 parts x 8 x 2
 constexpr int STEPB = 3 * 64 * 16;    // bytes of one reduction step of a 16-filter fragment
 
-// Eight floats into three bf16 octets, each part the nearest to what the parts before it leave, so
-// that the products left out have no sign in common (cut off instead, they pull every sum towards
-// zero by 4e-8, which thousands of rows do not average out).  Values that would round up to an
-// infinity are cut off; infinities and NaN keep their value in the first part and zero (NaN) in the
-// others.
-__device__ __forceinline__ void split8(const float* x, uintx4& h, uintx4& m, uintx4& l) {
+// Values from here on take the branch of split8: some would round up to an infinity.
+constexpr float SPLIT_BIG = 3.3895e38f;
+__device__ __forceinline__ float max8(const float* x) {
     float big = 0.f;
 #pragma unroll
     for (int i = 0; i < 8; ++i) big = fmaxf(big, fabsf(x[i]));
+    return big;
+}
+
+// Eight floats into three bf16 octets, each part the nearest to what the parts before it leave, so
+// that the products left out have no sign in common (cut off instead, they pull every sum towards
+// zero by 4e-8, which thousands of rows do not average out).  Values that would round up to an
+// infinity are cut off.  An infinity is a third part alone: it meets the first part of a weight, whose
+// sign is the weight's, and not the others.  NaN is NaN in every part.  ANY = false: without the branch
+// these take, for finite values below SPLIT_BIG (and NaN).
+template <bool ANY = true>
+__device__ __forceinline__ void split8(const float* x, uintx4& h, uintx4& m, uintx4& l) {
+    const float big = ANY ? max8(x) : 0.f;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const floatx2 v = {x[2 * i], x[2 * i + 1]};
         unsigned p = __builtin_bit_cast(unsigned, __builtin_convertvector(v, bf16x2));
-        if (big >= 3.3895e38f) {
-            if (fabsf(v[0]) >= 3.3895e38f) p = (p & 0xffff0000u) | __float_as_uint(v[0]) >> 16;
-            if (fabsf(v[1]) >= 3.3895e38f) p = (p & 0xffffu) | (__float_as_uint(v[1]) & 0xffff0000u);
+        if (big >= SPLIT_BIG) {
+            const unsigned t0 = fabsf(v[0]) == INFINITY ? 0u : __float_as_uint(v[0]) >> 16;
+            const unsigned t1 = fabsf(v[1]) == INFINITY ? 0u : __float_as_uint(v[1]) & 0xffff0000u;
+            if (fabsf(v[0]) >= SPLIT_BIG) p = (p & 0xffff0000u) | t0;
+            if (fabsf(v[1]) >= SPLIT_BIG) p = (p & 0xffffu) | t1;
         }
-        floatx2 r = {v[0] - __uint_as_float(p << 16), v[1] - __uint_as_float(p & 0xffff0000u)};
-        if (big >= 3.3895e38f) {
-            if (fabsf(v[0]) == INFINITY) r[0] = 0.f;
-            if (fabsf(v[1]) == INFINITY) r[1] = 0.f;
-        }
-        const unsigned q = __builtin_bit_cast(unsigned, __builtin_convertvector(r, bf16x2));
-        const floatx2 t = {r[0] - __uint_as_float(q << 16), r[1] - __uint_as_float(q & 0xffff0000u)};
-        h[i] = p;
-        m[i] = q;
-        l[i] = __builtin_bit_cast(unsigned, __builtin_convertvector(t, bf16x2));
-    }
-}
-
-// The same without a branch, for matrix instructions that are scheduled among these: the first two parts
-// are clamped to the largest bf16 instead, so that no finite value rounds up to an infinity, and an
-// infinity (NaN) ends up in the third part, behind two finite ones of its sign.  Twelve more instructions
-// an octet: the convolutions, which stage between their stages, are 5 to 9 % slower with it.
-__device__ __forceinline__ void split8_clamped(const float* x, uintx4& h, uintx4& m, uintx4& l) {
-    constexpr float top = 3.38953139e38f;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const floatx2 v = {x[2 * i], x[2 * i + 1]};
-        const floatx2 vc = {__builtin_amdgcn_fmed3f(v[0], -top, top), __builtin_amdgcn_fmed3f(v[1], -top, top)};
-        const unsigned p = __builtin_bit_cast(unsigned, __builtin_convertvector(vc, bf16x2));
         const floatx2 r = {v[0] - __uint_as_float(p << 16), v[1] - __uint_as_float(p & 0xffff0000u)};
-        const floatx2 rc = {__builtin_amdgcn_fmed3f(r[0], -top, top), __builtin_amdgcn_fmed3f(r[1], -top, top)};
-        const unsigned q = __builtin_bit_cast(unsigned, __builtin_convertvector(rc, bf16x2));
+        unsigned q = __builtin_bit_cast(unsigned, __builtin_convertvector(r, bf16x2));
+        if (big >= SPLIT_BIG) {
+            if (fabsf(r[0]) == INFINITY) q &= 0xffff0000u;
+            if (fabsf(r[1]) == INFINITY) q &= 0xffffu;
+        }
         const floatx2 t = {r[0] - __uint_as_float(q << 16), r[1] - __uint_as_float(q & 0xffff0000u)};
         h[i] = p;
         m[i] = q;
@@ -65,7 +55,7 @@ __device__ __forceinline__ void split8_clamped(const float* x, uintx4& h, uintx4
     }
 }
 
-// The parts of a filter weight, cut off (each part has the sign of the weight), to dst, dst + 512 and
+// The parts of a filter weight, each the nearest to what the parts before it leave, to dst, dst + 512 and
 // dst + 1024.  A part of a nonzero weight is never zero (the smallest normal instead), so that an
 // infinite operand gives the infinity an FP32 product gives and no 0 x inf.
 __device__ __forceinline__ void split_weight(float w, unsigned short* dst) {
@@ -73,6 +63,7 @@ __device__ __forceinline__ void split_weight(float w, unsigned short* dst) {
 #pragma unroll
     for (int s = 0; s < 3; ++s) {
         unsigned h = __float_as_uint(r) >> 16;
+        if (fabsf(r) < SPLIT_BIG) h = __builtin_bit_cast(unsigned, __builtin_convertvector(floatx2{r, 0.f}, bf16x2)) & 0xffffu;
         r -= __uint_as_float(h << 16);
         if (w != 0.f && (h & 0x7fff) == 0) h = (__float_as_uint(w) >> 16 & 0x8000) | 0x0080;
         dst[s * 512] = (unsigned short)h;
