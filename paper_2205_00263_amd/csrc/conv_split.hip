@@ -2,7 +2,7 @@
 // the adjoint and the transposed convolution of back-substitution (Eq. 2), from input windows staged in
 // LDS.
 //
-// Operands.  Each FP32 value is cut into three bf16 parts that add up to it exactly, x = x0 + x1 + x2,
+// Operands.  Each FP32 value is cut into three bf16 parts that add up to it (from 2^-110 on), x = x0 + x1 + x2,
 // each the nearest to what is left, and a product is the sum of the six part products x_i w_j with
 // i + j <= 2, accumulated in FP32 by v_mfma_f32_16x16x32_bf16.  x1 and w1 are at most 2^-8, x2 and w2
 // 2^-17 of their value's leading power of two, so the three products left out are at most 2^-24 + 2^-34 of

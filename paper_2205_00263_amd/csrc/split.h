@@ -56,16 +56,18 @@ __device__ __forceinline__ void split8(const float* x, uintx4& h, uintx4& m, uin
 }
 
 // The parts of a filter weight, each the nearest to what the parts before it leave, to dst, dst + 512 and
-// dst + 1024.  A part of a nonzero weight is never zero (the smallest normal instead), so that an
-// infinite operand gives the infinity an FP32 product gives and no 0 x inf.
+// dst + 1024.  The first part of a nonzero weight is never zero (the smallest bf16 number instead, which the
+// second then takes back), so that an infinite operand gives the infinity an FP32 product gives and no
+// 0 x inf.  The matrix instruction keeps denormal parts; what a weight below 2^-110 has under 2^-133, the
+// smallest bf16 number, is rounded away.
 __device__ __forceinline__ void split_weight(float w, unsigned short* dst) {
     float r = w;
 #pragma unroll
     for (int s = 0; s < 3; ++s) {
         unsigned h = __float_as_uint(r) >> 16;
         if (fabsf(r) < SPLIT_BIG) h = __builtin_bit_cast(unsigned, __builtin_convertvector(floatx2{r, 0.f}, bf16x2)) & 0xffffu;
+        if (s == 0 && w != 0.f) h |= (h & 0x7fff) == 0;
         r -= __uint_as_float(h << 16);
-        if (w != 0.f && (h & 0x7fff) == 0) h = (__float_as_uint(w) >> 16 & 0x8000) | 0x0080;
         dst[s * 512] = (unsigned short)h;
     }
 }

@@ -74,6 +74,17 @@ def test_one_term(kind, dims):
     assert np.linalg.norm(err) <= 1.065 * np.linalg.norm(f32), np.linalg.norm(err) / np.linalg.norm(f32)
 
 
+@pytest.mark.parametrize("kind,dims", [("conv", (16, 9, 32, 3, 1, 1)), ("conv", (16, 8, 32, 4, 2, 1)), ("fc", FCS[0]),
+                                       ("fc", FCS[3])])
+@pytest.mark.parametrize("w_exp", [-100, -110, -120])
+def test_tiny_weights(kind, dims, w_exp):
+    """Weights whose lower parts end below FP32's smallest normal number, against operands that bring the products
+    back: a part is a multiple of 2^-133 (the smallest bf16 number), so the weight is right to half of that."""
+    rng = np.random.default_rng(sum(dims) - w_exp)
+    for out, ref in _products(kind, dims, rng, x_exp=100, w_exp=w_exp):
+        assert np.all(np.abs(out - ref) <= (2.0 ** -23 * (1 + 2.0 ** -4) + 2.0 ** (-134 - w_exp)) * np.abs(ref))
+
+
 @pytest.mark.parametrize("dims", [FCS[0], FCS[3]])
 def test_infinite_terms_large_weights(dims):
     """An infinite term of a fully connected product meets weights whose lower parts have the other sign, and
