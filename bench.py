@@ -501,17 +501,44 @@ def bab_run(args):
                       "queries": res}), flush=True)
 
 
-def roofline_of(kstats, traffic=None):
+def split_products(nodes, kind, node, variants=0):
+    """Whether the products of a node (kind fc_* or conv_*) take the bf16 matrix instructions with split
+    operands (csrc/fc_split.hip, plan_split in csrc/conv_split.hip and the tap form tried before it in
+    csrc/conv_rows.hip); node < 0: any node's of that kind."""
+    import paper_2205_00263_amd as P
+    import workloads as W
+    if node < 0:
+        return any(split_products(nodes, kind, i, variants) for i in range(len(nodes)))
+    op, _, form = kind.partition("_")
+    n = nodes[node]
+    if form not in ("forward", "backsub") or n["kind"] != op:
+        return False
+    if op == "fc":
+        return True
+    shapes = W.node_shapes(nodes)
+    (ci, hi, wi), (co, ho, wo) = shapes[n["src"]], shapes[node]
+    k, s, p = n["W"].shape[2], n["stride"], n["pad"]
+    if variants & P.VARIANTS["no_win_conv"]:
+        return False
+    if form == "forward":
+        return ci % 8 == 0 and co % 16 == 0 and (k, s) in ((3, 1), (2, 1), (4, 2), (3, 2), (1, 2))
+    taps = (s == 2 and k <= 4 and co == 32 and 16 < ho * wo <= 32 and hi * wi <= 192 and 2 <= ci <= 16 and
+            not variants & (P.VARIANTS["no_tap_convt"] | P.VARIANTS["no_row_conv"]))
+    return (co % 8 == 0 and ci % 16 == 0 and not taps and
+            ((s == 1 and k in (2, 3) and p <= k - 1) or (s == 2 and k in (1, 3, 4) and min(hi, wi) >= 2)))
+
+
+def roofline_of(kstats, traffic=None, split=False):
     """Roofline object of one timed kernel class: its bound follows from its algorithmic intensity
-    against the MI355X ridge point (FP32 MFMA 157.3 TFLOP/s over HBM 8 TB/s = 19.7 flop/byte).  The
-    convolutions and fully connected products take six bf16 part products for an FP32 one, at 2516
-    TFLOP/s dense: 419.4 TFLOP/s, 52.4 flop/byte."""
+    against the MI355X ridge point (FP32 MFMA 157.3 TFLOP/s over HBM 8 TB/s = 19.7 flop/byte).
+    Products on split operands take six bf16 part products for an FP32 one, at 2516 TFLOP/s dense:
+    419.4 TFLOP/s, 52.4 flop/byte (a class over all nodes is priced so if any of them takes it)."""
     if not kstats or kstats["count"] == 0:
         return None
     avg_s = kstats["ms"] / kstats["count"] / 1e3
     flops = kstats["flops"] / kstats["count"]
     byts = kstats["bytes"] / kstats["count"]
-    peak = 2516.6 / 6 if kstats["name"].startswith(("conv_", "fc_")) else 157.3
+    peak = 2516.6 / 6 if split else 157.3
     ridge = peak * 1e12 / 8.0e12
     if byts > 0 and (flops == 0 or flops / byts < ridge):
         achieved = byts / avg_s / 1e9
@@ -576,7 +603,8 @@ def convsmall_batch(args):
     kstats = timer.stop()
     n_bounded = args.batch * args.steps
     value = n_bounded / el
-    roof = roofline_of(kstats, measured_traffic("convsmall", args.roofline_kernel))
+    roof = roofline_of(kstats, measured_traffic("convsmall", args.roofline_kernel),
+                       split_products(wl.nodes, args.roofline_kernel, -1, P.get_kernel_variants()))
     out = {
         "metric": "BaB subproblems bounded/sec (alpha,beta-optimised, 20 Adam steps) + p50/p99 batch latency",
         "value": round(value, 2), "unit": "subproblems/s", "n_gpus": 1, "steps": args.steps,
@@ -793,7 +821,8 @@ def convbig_batch(args):
                    "step_p99_ms": round(float(np.percentile(lat, 99)) * 1e3, 3)},
         "bound_summary": {"root_lb_min": float(root_lb.min()), "root_ub_min": float(root_ub.min()),
                           "batch_lb_mean": float(lb.min(1).mean())},
-        "roofline": roofline_of(kstats, measured_traffic("convbig", kind, node)),
+        "roofline": roofline_of(kstats, measured_traffic("convbig", kind, node),
+                                split_products(wl.nodes, kind, node, P.get_kernel_variants())),
     }
     if args.stream_queries > 0:
         log(f"query stream: {args.stream_queries} queries")
