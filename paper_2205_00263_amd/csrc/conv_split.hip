@@ -2,13 +2,13 @@
 // the adjoint and the transposed convolution of back-substitution (Eq. 2), from input windows staged in
 // LDS.
 //
-// Operands.  Each FP32 value is cut into three bf16 parts that add up to it (from 2^-110 on), x = x0 + x1 + x2,
-// each the nearest to what is left, and a product is the sum of the six part products x_i w_j with
-// i + j <= 2, accumulated in FP32 by v_mfma_f32_16x16x32_bf16.  x1 and w1 are at most 2^-8, x2 and w2
-// 2^-17 of their value's leading power of two, so the three products left out are at most 2^-24 + 2^-34 of
-// the product (2^-27.4 in the mean square of 4e6 random pairs) and have no preferred sign.  That shows
-// in a sum of one term alone, off by up to 1.0e-7 (2.6e-8 in the mean square) where FP32's rounding is by
-// 6.0e-8 (2.5e-8); with weights cut off instead of rounded it was 2.0e-7 (3.1e-8).
+// Operands.  Each FP32 value is cut into three bf16 parts that add up to it (from 2^-110 on; below, to
+// 2^-134), x = x0 + x1 + x2, each the nearest to what is left, and a product is the sum of the six part
+// products x_i w_j with i + j <= 2, accumulated in FP32 by v_mfma_f32_16x16x32_bf16.  x1 and w1 are at most
+// 2^-8, x2 and w2 2^-17 of their value's leading power of two, so the three products left out are at most
+// 2^-24 + 2^-34 of the product (2^-27.4 in the mean square of 4e6 random pairs) and have no preferred sign.
+// That shows in a sum of one term alone, off by up to 1.0e-7 (2.6e-8 in the mean square) where FP32's
+// rounding is by 6.0e-8 (2.5e-8); with weights cut off instead of rounded it was 2.0e-7 (3.1e-8).
 // Six instructions of 16 cycles for 32 terms of a 16x16 tile take 96 cycles where the FP32 instruction
 // takes 256, so the FP32 matrix rate (154 TFLOP/s measured) no longer bounds the layer: the bf16
 // instruction sustains 2.0 PFLOP/s, 333 TFLOP/s of such products.  The activations are cut while they
@@ -23,6 +23,9 @@
 // round the large sum once more each.  Error of a layer against FP64: 7.6e-8, 1.1e-7 and 5.6e-8 back
 // through ConvBig's three layers, where the FP32 instructions give 2.1e-7, 3.2e-7 and 1.4e-7 (mean of the
 // errors 1e-10 of the values in both); of the fourth layer's bounds 2.0e-7 against 2.3e-7.
+//
+// Infinities and NaN give what FP32 products give (see split8); so does a product beyond FP32's range, or
+// NaN from 2^8 times it on, where the small part products leave it too.
 //
 // Work split.  One workgroup owns BM output positions (part of a row's grid, or the whole grids of R
 // rows) and BN filters.  Per stage of CGS 8-channel groups it writes the input window those positions
@@ -517,7 +520,8 @@ Shape shape_of(const View& v, int pat, int pad, int cgs, const Tile& t) {
     return s;
 }
 
-// Tiles that serve Cout channels, the one for large batches first.
+// Tiles that serve Cout channels, the preferred one first (launch_split leaves it where another one's
+// positions are better filled).
 int tiles_for(int pat, int Cout, Tile* t) {
     int n = 0;
     if (pat_np(pat) == 1) {

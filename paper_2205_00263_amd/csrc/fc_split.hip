@@ -12,7 +12,7 @@
 // stream, laid out in the order the wavefronts read it.  The cutting is as long as the matrix work that
 // follows from it, so it has no branch and its instructions are interleaved with the matrix ones; octets that
 // need the branch (infinities, values that round up to one) are cut again behind them.
-// 9216 rows of 4096 -> 512 back: 254 us (152 TFLOP/s), 391 us on the FP32 instructions before.
+// 9216 rows of 4096 -> 512 back: 250 us (155 TFLOP/s), 391 us on the FP32 instructions before.
 //
 // k_fc_parts, for few: a wavefront per part and 16 rows x 32 outputs per workgroup, operands straight
 // into registers, one exchange through LDS at the end.  A layer of few rows was a chain of K / 16 loads

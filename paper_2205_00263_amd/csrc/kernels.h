@@ -80,8 +80,8 @@ bool launch_conv_first(const ConvGeom& g, const float* G, float* C, int M, bool 
                        const ConeClip* clip = nullptr);
 // Convolutions on the bf16 matrix instructions with exactly split FP32 operands, from input windows
 // staged in LDS (input channels a multiple of 8, output channels of 16; 3x3 / 1, 2x2 / 1, 3x3 / 2,
-// 4x4 / 2 and 1x1 / 2 filters); false (nothing launched) for other shapes.  split_stream_bytes plans a direction and gives the size of its filter stream (0: not
-// covered), launch_split_stream fills it.
+// 4x4 / 2 and 1x1 / 2 filters); false (nothing launched) for other shapes.  split_stream_bytes plans a
+// direction and gives the size of its filter stream (0: not covered), launch_split_stream fills it.
 size_t split_stream_bytes(ConvGeom& g, bool back);
 void launch_split_stream(ConvGeom& g, bool back, void* out, hipStream_t st);
 bool launch_conv_forward_split(const ConvGeom& g, const float* G, float* C, int M, bool accumulate, hipStream_t st,
