@@ -40,7 +40,7 @@
 // An output sums its stages, window offsets and part products in an order fixed by the layer, whatever
 // the batch and tile: a row's result does not depend on the rows around it.
 //
-// What bounds it, by its counters: the matrix units are busy 42 to 59 % of the time; the rest is the cutting
+// What bounds it, by its counters: the matrix units are busy 38 to 59 % of the time; the rest is the cutting
 // and writing of the window between two barriers and, at 4x4 / 2, the wait for the input itself.  2048
 // rows of 32x16x16 -> 64 (3x3) take 100 us (190 TFLOP/s; 207 us on the FP32 instructions before); without
 // its global loads and stores the kernel takes 75 us, with them alone 40.  32x32x32 -> 32x16x16 (4x4 / 2):
