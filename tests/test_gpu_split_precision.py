@@ -102,3 +102,34 @@ def test_infinite_terms_large_weights(dims):
         x[np.arange(M), at] = sign * np.inf
         out = _run(net, name, x, n_out)
         assert np.array_equal(out, np.where(wt[at] * sign[:, None] > 0, np.inf, -np.inf))
+
+
+@pytest.mark.parametrize("dims", [CONVS[0], CONVS[3], CONVS[5], CONVS[6]])
+def test_infinite_terms_large_weights_convolutions(dims):
+    """The same for convolutions, with a finite value next to FP32's largest number elsewhere in the row: it is
+    cut off, not rounded to an infinity, and its products with 2^-120 are exact to FP32 accuracy."""
+    P = _P()
+    ci, h, co, k, s, p = dims
+    for w_exp in (10, -120):
+        rng = np.random.default_rng(7)
+        nodes = _layer("conv", dims, rng, w_exp)
+        net, on = P.Net(nodes), onet.Net(nodes)
+        W = nodes[1]["W"].astype(np.float64)
+        for name, f, n_in, n_out in (("conv_forward", onet.conv_apply, on.sizes[0], on.sizes[1]),
+                                     ("conv_backsub", onet.conv_adjoint, on.sizes[1], on.sizes[0])):
+            M = 12
+            e = np.zeros((M, n_in))
+            e[np.arange(M), rng.integers(0, n_in, size=M)] = rng.choice([-1.0, 1.0], size=M)
+            hit = f(W, e, on.shapes[0], on.shapes[1], s, p)
+            if w_exp > 0:
+                x = rng.normal(size=(M, n_in)).astype(np.float32)
+                x[e != 0] = (e[e != 0] * np.inf).astype(np.float32)
+                out = _run(net, name, x, n_out)
+                assert np.array_equal(out == np.inf, hit > 0) and np.array_equal(out == -np.inf, hit < 0)
+                assert np.all(np.isfinite(out[hit == 0]))
+            else:
+                big = np.float32(3.4028e38)
+                out = _run(net, name, (e * big).astype(np.float32), n_out)
+                # cut off, the first part leaves up to 2^-7: twice the bound of rounded parts on each product left
+                # out; the weights (2^-120) are right to 2^-14
+                assert np.all(np.abs(out - hit * float(big)) <= (2.0 ** -22 + 2.0 ** -14) * np.abs(hit * float(big)))
